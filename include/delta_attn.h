@@ -312,7 +312,9 @@ da_status da_check_inputs(const int32_t* cu_seqlens, int B, int max_seqlen, int 
  * rows_per_wave query rows per wavefront) from these numbers instead of
  * restating the plan.  Each attention workgroup holds waves_per_block
  * wavefronts: heads query heads of one GQA group, each with waves_per_block /
- * heads row sub-tiles of rows_per_wave rows.  The strided dense rows split
+ * heads row sub-tiles of rows_per_wave rows.  (Small launches, short windows
+ * and d = 64 run workgroups of half as many wavefronts; each wavefront's rows
+ * and tiles are the same.)  The strided dense rows split
  * their key axis into key_chunks chunks of chunk_keys keys.
  * Returns DA_ERR_NULL without `plan`, otherwise the status the whole-path
  * call would return for these sizes before touching the device.

@@ -48,16 +48,16 @@ bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 }  // namespace
 
 // Query heads of one GQA group that share an attention workgroup: the
-// largest power of two dividing G, at most kAttnWaves.
-int heads_per_block(int G) {
+// largest power of two dividing G, at most its wavefronts.
+int heads_per_block(int G, int waves) {
   int h = 1;
-  while (h * 2 <= kAttnWaves && G % (h * 2) == 0) h *= 2;
+  while (h * 2 <= waves && G % (h * 2) == 0) h *= 2;
   return h;
 }
 
-int fused_heads_per_block(int G, int gamma, int max_rows) {
-  for (int h = heads_per_block(G); h >= 1; h /= 2) {
-    const int slab = kRowsPerWave * (kAttnWaves / h);
+int fused_heads_per_block(int G, int gamma, int max_rows, int waves) {
+  for (int h = heads_per_block(G, waves); h >= 1; h /= 2) {
+    const int slab = kRowsPerWave * (waves / h);
     if (G % h == 0 && slab % gamma == 0 && slab <= max_rows) return h;
   }
   return 0;
@@ -155,6 +155,123 @@ da_status validate(const Problem& P, bool need_window, bool need_gamma) {
   return DA_OK;
 }
 
+constexpr int kCUs = 256;
+enum class Launch { kSparseRows, kDenseCausal, kStridedRows };
+
+// Wavefronts per attention workgroup: kAttnWaves, or half of them.  `blocks` is
+// the launch in 8-wave workgroups (equivalents of the longest one), `keys` the
+// keys of a sparse row.  Outputs are bitwise the same either way: a wavefront
+// runs the same rows over the same tiles.
+//
+// Half-size workgroups fit a CU twice at d = 128 (registers: one wavefront per
+// SIMD each), so that one's first loads and last stores run beside the other's
+// tiles, and spread a small launch over more CUs; each K/V tile then serves
+// 128 rows instead of 256, which costs a long launch 2-4 % in L2 traffic and
+// power.  At d = 64 three fit (12 wavefronts per CU in place of 8), which
+// always pays.  Measured on an MI355X, 8 -> 4 wavefronts:
+//   d = 64: 16-head sparse rows, window 1024, 38K tokens 282 -> 223 us; Delta
+//     prefill 131K tokens, 32 heads 6.01 -> 5.34 ms; dense 16K 1.16 -> 1.06 ms;
+//   d = 128, launches below one round of the CUs: dense 512-2048 tokens, 32
+//     heads 18.7 -> 14.3 and 52.1 -> 45.4 us, sparse 1K tokens 28.5 -> 23.8 us;
+//   d = 128, few keys per row (the fixed cost of a workgroup then outweighs its
+//     tiles), 32K tokens, 32 heads: window 64 200 -> 183 us, 256 275 -> 261 us,
+//     512 383 -> 377 us, 1024 593 -> 599 us; with 8 heads (one per workgroup,
+//     whose 256 rows reach further past the window) 1024 161 -> 156 us, 2048
+//     265 -> 268 us;
+//   d = 128, a last round of at most half the CUs' places: 8 heads, window
+//     2048, 352 blocks 122 -> 106 us, 640 blocks 187 -> 172 us; but 256 blocks
+//     64.5 -> 68.6 us and 480 blocks 126 -> 133 us (whole rounds), and 32
+//     heads, 2080 blocks 513 -> 525 us.
+int attn_waves(Launch kind, int d, int heads, int64_t blocks, int64_t keys) {
+  constexpr int kHalf = kAttnWaves / 2;
+  if (d == 64) return kHalf;
+  if (kind == Launch::kSparseRows) {
+    if (keys <= (heads == 1 ? 1024 : 512)) return kHalf;
+    if (blocks < kCUs) return kHalf;
+  } else if (blocks <= kCUs * 11 / 8) {
+    // (workgroups of unequal length, longest first: 352 blocks of dense rows
+    // 75.8 -> 67.8 us, 416 blocks 90.7 -> 94.7 us)
+    return kHalf;
+  }
+  if (blocks > 4 * kCUs || kind == Launch::kDenseCausal) return kAttnWaves;
+  // Rounds in hundredths: a half-size workgroup alone on its CU takes about 0.6
+  // of the time that two take together, and a full round 4 % longer.
+  const int64_t rest = 2 * blocks % (2 * kCUs);
+  const int64_t r8 = (blocks + kCUs - 1) / kCUs * 100;
+  const int64_t r4 = 2 * blocks / (2 * kCUs) * 104 + (rest == 0 ? 0 : rest <= kCUs ? 62 : 104);
+  return r4 < r8 ? kHalf : kAttnWaves;
+}
+
+// Tiling of a launch over `rows` rows per (sequence, head) by workgroups of
+// `waves` wavefronts and `hpw` heads.
+void set_tiling(Args& a, int waves, int hpw, int rows) {
+  a.hpw = hpw;
+  a.ppw = waves / hpw;
+  a.n_hgroups = a.Hq / hpw;
+  const int rpb = kRowsPerWave * a.ppw;
+  a.n_rtiles = (int)(((int64_t)rows + rpb - 1) / rpb);
+}
+
+// Workgroups of a launch over `rows` rows per (sequence, head) and `split` parts.
+int64_t n_blocks(const Problem& P, int waves, int hpw, int64_t rows, int split) {
+  const int64_t rpb = kRowsPerWave * (waves / hpw);
+  return (int64_t)P.B * (P.Hq / hpw) * split * ((rows + rpb - 1) / rpb);
+}
+
+// Tiles the sparse launch; in the fused schedule gamma and the list blocks bind
+// the row slab.
+void tile_sparse(Args& a, const Problem& P, bool fused) {
+  const int G = P.Hq / P.Hkv;
+  const int max_rows = P.blk_ptr ? P.block_q : INT32_MAX;
+  auto heads = [&](int waves) {
+    return fused ? fused_heads_per_block(G, P.gamma, max_rows, waves) : heads_per_block(G, waves);
+  };
+  const int h8 = heads(kAttnWaves);
+  const int64_t keys = P.blk_ptr ? INT64_MAX : (int64_t)P.window + P.n_sink;
+  int waves = attn_waves(Launch::kSparseRows, P.d, h8, n_blocks(P, kAttnWaves, h8, P.N, 1), keys);
+  // (a slab of half the rows may hold no whole group, and twice the blocks may
+  // pass the grid's limit)
+  if (waves < kAttnWaves &&
+      (heads(waves) == 0 || n_blocks(P, waves, heads(waves), P.N, 1) > INT32_MAX))
+    waves = kAttnWaves;
+  set_tiling(a, waves, heads(waves), P.N);
+}
+
+// Tiles the dense causal launch.
+void tile_dense(Args& a, const Problem& P) {
+  const int G = P.Hq / P.Hkv;
+  const int h8 = heads_per_block(G);
+  int waves = attn_waves(Launch::kDenseCausal, P.d, h8, n_blocks(P, kAttnWaves, h8, P.N, 1), 0);
+  if (n_blocks(P, waves, heads_per_block(G, waves), P.N, 1) > INT32_MAX) waves = kAttnWaves;
+  set_tiling(a, waves, heads_per_block(G, waves), P.N);
+}
+
+// Key tiles all strided-row workgroups of kAttnWaves wavefronts run together:
+// row tiles of rpb rows, the anchors' growing with their position, those of
+// `tail` further rows reaching over the whole sequence.
+int64_t strided_tiles(int64_t B, int64_t N, int Hq, int G, int64_t gamma, int64_t tail) {
+  const int hpw = heads_per_block(G);
+  const int64_t rpb = kRowsPerWave * (kAttnWaves / hpw);
+  const int64_t T = (N + kKeyTile - 1) / kKeyTile;
+  const int64_t nA = N / gamma, ra = (nA + rpb - 1) / rpb;
+  int64_t per = (int64_t)((double)ra * (ra + 1) / 2 * rpb * gamma / kKeyTile);
+  if (per > ra * T) per = ra * T;
+  per += ((nA + tail + rpb - 1) / rpb - ra) * T;
+  return B * (Hq / hpw) * per;
+}
+
+// Tiles the strided dense rows: nR_max rows, nC chunks of `chunk` keys.
+void tile_strided(Args& a, const Problem& P, const Plan& plan) {
+  const int G = P.Hq / P.Hkv;
+  const int64_t tail = P.cu ? (int64_t)plan.nR_max - plan.nA_max : P.N % P.gamma;
+  const int64_t work = strided_tiles(P.B, P.N, P.Hq, G, P.gamma, tail);
+  int waves = attn_waves(Launch::kStridedRows, P.d, heads_per_block(G),
+                         work / (plan.chunk / kKeyTile), 0);
+  if (n_blocks(P, waves, heads_per_block(G, waves), plan.nR_max, plan.nC) > INT32_MAX)
+    waves = kAttnWaves;
+  set_tiling(a, waves, heads_per_block(G, waves), plan.nR_max);
+}
+
 Args base_args(const Problem& P) {
   Args a;
   memset(&a, 0, sizeof a);
@@ -184,11 +301,6 @@ Args base_args(const Problem& P) {
   }
   a.gamma = P.gamma > 0 ? P.gamma : 1;
   a.scale_log2 = (float)(1.4426950408889634 / sqrt((double)P.d));
-  a.hpw = heads_per_block(P.Hq / P.Hkv);
-  a.ppw = kAttnWaves / a.hpw;
-  a.n_hgroups = P.Hq / a.hpw;
-  const int rows_per_block = kRowsPerWave * a.ppw;
-  a.n_rtiles = (P.N + rows_per_block - 1) / rows_per_block;
   a.head_chunk = 8192 / P.d;
   return a;
 }
@@ -199,6 +311,10 @@ da_status run_plain(const Problem& P, bool sparse, void* stream) {
   st = check_device();
   if (st != DA_OK) return st;
   Args a = base_args(P);
+  if (sparse)
+    tile_sparse(a, P, false);
+  else
+    tile_dense(a, P);
   hipError_t e = sparse ? launch_sparse(a, (hipStream_t)stream) : launch_dense(a, (hipStream_t)stream);
   if (e != hipSuccess) return fail_hip(e);
   return DA_OK;
@@ -284,7 +400,7 @@ da_status run_delta(const Problem& P, void* workspace, size_t workspace_bytes, v
     a.fuse = corr_mode == DA_CORR_RECOMPUTE ? 2 : 1;
     if (steps & DA_STEP_DENSE_ROWS) {
       Args ar = a;
-      ar.n_rtiles = (plan.nR_max + kRowsPerWave * a.ppw - 1) / (kRowsPerWave * a.ppw);
+      tile_strided(ar, P, plan);
       e = launch_dense_rows(ar, s);
       if (e != hipSuccess) return fail_hip(e);
     }
@@ -294,10 +410,7 @@ da_status run_delta(const Problem& P, void* workspace, size_t workspace_bytes, v
     }
     if (steps & DA_STEP_SPARSE) {
       Args as = a;
-      as.hpw = fhpw;
-      as.ppw = kAttnWaves / fhpw;
-      as.n_hgroups = P.Hq / fhpw;
-      as.n_rtiles = (P.N + kRowsPerWave * as.ppw - 1) / (kRowsPerWave * as.ppw);
+      tile_sparse(as, P, true);
       e = launch_sparse(as, s);
       if (e != hipSuccess) return fail_hip(e);
     }
@@ -305,13 +418,15 @@ da_status run_delta(const Problem& P, void* workspace, size_t workspace_bytes, v
   }
   // Step 1: sparse attention for every row (+ fp32 copy at anchors).
   if (steps & DA_STEP_SPARSE) {
-    e = launch_sparse(a, s);
+    Args as = a;
+    tile_sparse(as, P, false);
+    e = launch_sparse(as, s);
     if (e != hipSuccess) return fail_hip(e);
   }
   // Steps 2-3: dense attention at anchors and tail rows, key axis split in chunks.
   if (steps & DA_STEP_DENSE_ROWS) {
     Args ar = a;
-    ar.n_rtiles = (plan.nR_max + kRowsPerWave * a.ppw - 1) / (kRowsPerWave * a.ppw);
+    tile_strided(ar, P, plan);
     e = launch_dense_rows(ar, s);
     if (e != hipSuccess) return fail_hip(e);
   }

@@ -14,12 +14,12 @@ namespace da {
 // Keys per tile of every attention kernel, and query rows per wavefront.
 constexpr int kKeyTile = 64;
 constexpr int kRowsPerWave = 32;
-// Attention workgroups: kAttnWaves wavefronts share every K/V tile, which
-// passes through a ring of kAttnStages LDS buffers (prefetch distance
-// kAttnStages - 1 tiles).
+// Attention workgroups: kAttnWaves wavefronts, or half of them in the launches
+// that da_api.cpp's attn_waves names, share every K/V tile, which passes
+// through a ring of kAttnStages LDS buffers (prefetch distance kAttnStages - 1
+// tiles).
 constexpr int kAttnWaves = 8;
 constexpr int kAttnStages = 2;
-constexpr int kAttnThreads = 64 * kAttnWaves;
 // Delta epilogue workgroups.
 constexpr int kEpiThreads = 256;
 
@@ -71,7 +71,7 @@ struct Args {
   int block_q, nqb;
 
   // Workgroup tiling of (query heads x rows): hpw heads of one kv group, each
-  // with ppw sub-tiles of 32 rows; hpw * ppw == kAttnWaves.
+  // with ppw sub-tiles of 32 rows; hpw * ppw wavefronts, kAttnWaves or half of it.
   int hpw, ppw;
   int n_hgroups;      // Hq / hpw
   int n_rtiles;       // row tiles (of 32 * ppw rows) per (sequence, head group)
@@ -127,11 +127,11 @@ constexpr size_t kScratchBytes = DA_NOALLOC_SCRATCH_BYTES;
 hipError_t scratch_address(int dev, void** p);
 // Extra workspace floats the correction variants need beyond the plan.
 size_t correction_floats(int B, int max_seqlen, int Hq, int d, int gamma, int mode);
-int heads_per_block(int G);
+int heads_per_block(int G, int waves = kAttnWaves);
 // Heads per workgroup of the fused sparse kernel: the largest power of two
-// dividing G (at most kAttnWaves) whose per-head row slab, 32 * kAttnWaves /
-// hpw rows, is a multiple of gamma and at most max_rows; 0 when there is none.
-int fused_heads_per_block(int G, int gamma, int max_rows);
+// dividing G (at most `waves`) whose per-head row slab, 32 * waves / hpw rows,
+// is a multiple of gamma and at most max_rows; 0 when there is none.
+int fused_heads_per_block(int G, int gamma, int max_rows, int waves = kAttnWaves);
 
 // Kernel launchers (da_kernels.hip).  Each returns the hipError_t of the launch.
 hipError_t launch_sparse(const Args& a, hipStream_t s);

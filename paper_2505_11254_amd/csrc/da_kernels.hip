@@ -54,13 +54,13 @@ enum MaskKind { kMaskCausal = 2, kMaskWindow = 3, kMaskBoth = 4, kMaskAll = 5 };
 //      operand reads of 16 consecutive keys over all banks;
 //   V: chunk c of key row r sits at c ^ vswz(r), which spreads the transposing
 //      8-byte reads (four keys x sixteen dims per 16-lane group).
-template <int D>
+template <int D, int NW>
 struct Lds {
   static constexpr int kElems = kKeyTile * D;
   static constexpr int vElems = kKeyTile * D;
   static constexpr int stageElems = kElems + vElems;
   static constexpr int kRegions = kKeyTile * D * 2 / 1024;  // 1 KB DMA regions per tile
-  static constexpr int kRegionsPerWave = kRegions / kAttnWaves;
+  static constexpr int kRegionsPerWave = kRegions / NW;
   __device__ static constexpr int kswz(int r) { return D == 128 ? (r & 15) : ((r >> 1) & 7); }
   __device__ static constexpr int vswz(int r) {
     return D == 128 ? ((r & 3) << 2) : (((r >> 1) & 1) << 2);
@@ -190,16 +190,25 @@ __device__ __forceinline__ int row_pos(int r, int nA, int Lc, int gamma) {
   return r;
 }
 
-template <int D, int MODE>
-__global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(2)))
+// LDS bytes of one workgroup: the K/V ring, then, for the sparse kernel, the
+// fp32 dense rows of its anchors (`pre_bytes`) and the staging of the queries
+// of wavefronts past the fourth.
+template <int D, int MODE, int NW>
+constexpr int lds_bytes(int pre_bytes) {
+  return kAttnStages * Lds<D, NW>::stageElems * 2 +
+         (MODE == kSparse ? pre_bytes + (NW > 4 ? (NW - 4) * kRowsPerWave * D * 2 : 0) : 0);
+}
+
+template <int D, int MODE, int NW>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 64 && NW == 4 ? 3 : 2)))
 void attn_kernel(Args a) {
-  using LD = Lds<D>;
+  using LD = Lds<D, NW>;
   constexpr int NS = kAttnStages;
+  constexpr int kThreads = 64 * NW;
+  extern __shared__ __attribute__((aligned(16))) uint16_t smem[];
   // The sparse kernel also holds, after the K/V ring, the fp32 dense rows of
   // its block's anchors for the fused store: hpw * (slab rows / gamma) rows
-  // of D floats, at most 128 * D floats (gamma >= 2).
-  constexpr int kPreFloats = (MODE == kSparse) ? 128 * D : 0;
-  __shared__ __attribute__((aligned(16))) uint16_t smem[NS * LD::stageElems + 2 * kPreFloats];
+  // of D floats.
   float* const dpre = (float*)(smem + NS * LD::stageElems);
 
   const int tid = threadIdx.x;
@@ -617,7 +626,7 @@ void attn_kernel(Args a) {
   // (the only tile that can end inside the sequence's last 64 keys) clears
   // the ring first, so that no stage can hold bits left by an earlier kernel.
   if (n_iter <= NS) {
-    for (int i = tid; i < NS * LD::stageElems / 8; i += kAttnThreads)
+    for (int i = tid; i < NS * LD::stageElems / 8; i += kThreads)
       *(u32x4*)(smem + 8 * i) = u32x4{0u, 0u, 0u, 0u};
     __syncthreads();
   }
@@ -649,15 +658,14 @@ void attn_kernel(Args a) {
   // instead: whole rows (four per instruction at d = 128), each lane fetching
   // the 16-byte chunk that lands, XOR-swizzled by row, at its place in LDS.
   // The staging is free LDS: ring stage 1 (filled only after the first
-  // barrier) for waves 0-3, the upper half of the dense-row area for waves
-  // 4-7 (when the staged dense rows fit the lower half).  Each lane reads its
-  // fragments from there.  Read straight into the fragment layout, every load
+  // barrier) for waves 0-3, the space behind the dense rows for waves 4-7.
+  // Each lane reads its fragments from there.  Read straight into the fragment layout, every load
   // instruction fetched 32 bytes of each of 32 rows, and at every block's start
   // those loads queued behind each other in the memory pipeline.
   constexpr int QCPR = D / 8;  // 16-byte chunks per query row
-  const bool q_lds = MODE == kSparse && nvec * 4 <= 64 * D;
+  constexpr bool q_lds = MODE == kSparse;
   uint16_t* const qst = smem + (wave < 4 ? LD::stageElems + wave * (kRowsPerWave * D)
-                                         : NS * LD::stageElems + 128 * D + (wave - 4) * (kRowsPerWave * D));
+                                         : NS * LD::stageElems + nvec * 8 + (wave - 4) * (kRowsPerWave * D));
   if (q_lds) {
     static_assert(NS == 2 && 4 * kRowsPerWave * D <= LD::stageElems, "query staging fits stage 1");
     constexpr int RPI = 64 / QCPR;  // rows per DMA instruction
@@ -699,7 +707,7 @@ void attn_kernel(Args a) {
     __builtin_amdgcn_s_waitcnt(0xC07F);
   }
   if (dsrc) *(f32x4*)(dpre + tid * 4) = dreg;
-  for (int u = tid + kAttnThreads; u < nvec; u += kAttnThreads)
+  for (int u = tid + kThreads; u < nvec; u += kThreads)
     if (const f32x4* src = dense_src(u)) *(f32x4*)(dpre + u * 4) = *src;
 
   // ---- main loop over a ring of NS LDS stages, one barrier per tile.  Step
@@ -846,7 +854,7 @@ void attn_kernel(Args a) {
     // bytes: four rows at d = 128) instead of 16 bytes of each of 32 rows
     // that lie Hq * d elements apart.  The wave reads only what it wrote (its
     // lanes exchange rows through wave_lds_exchange).
-    static_assert(NS * LD::stageElems >= kAttnWaves * kRowsPerWave * D, "output staging fits the ring");
+    static_assert(NS * LD::stageElems >= NW * kRowsPerWave * D, "output staging fits the ring");
     constexpr int CPR = D / 8;     // 16-byte chunks per row
     constexpr int RPI = 64 / CPR;  // rows per store instruction
     uint16_t* const stg = smem + wave * (kRowsPerWave * D);
@@ -883,7 +891,7 @@ void attn_kernel(Args a) {
     // that every store instruction writes whole rows (two of 512 bytes at
     // d = 128) instead of 32 bytes of each of 32 rows nC * D floats apart.
     __syncthreads();  // no wave reads the K/V ring any more
-    static_assert(NS * LD::stageElems * 2 >= kAttnWaves * 16 * D * 4, "partial staging fits the ring");
+    static_assert(NS * LD::stageElems * 2 >= NW * 16 * D * 4, "partial staging fits the ring");
     constexpr int CPR = D / 4;     // 16-byte chunks per fp32 row
     constexpr int RPI = 64 / CPR;  // rows per store instruction
     float* const stg = (float*)smem + wave * (16 * D);
@@ -1243,10 +1251,21 @@ hipError_t launch_attn(const Args& a0, hipStream_t s, int64_t nblocks) {
   a.fd_G = make_fastdiv((uint32_t)(a.Hq / a.Hkv));
   a.fd_gamma = make_fastdiv((uint32_t)a.gamma);
   a.fd_bq = make_fastdiv((uint32_t)(a.block_q > 0 ? a.block_q : 1));
-  if (a.d == 128)
-    hipLaunchKernelGGL((attn_kernel<128, MODE>), dim3((unsigned)nblocks), dim3(kAttnThreads), 0, s, a);
-  else
-    hipLaunchKernelGGL((attn_kernel<64, MODE>), dim3((unsigned)nblocks), dim3(kAttnThreads), 0, s, a);
+  // dense rows a sparse workgroup stages for the fused store
+  const int pre = MODE == kSparse && a.fuse && a.gamma > 1
+                      ? a.hpw * (kRowsPerWave * a.ppw / a.gamma) * a.d * 4 : 0;
+#define DA_ATTN(DD, W)                                                                          \
+  hipLaunchKernelGGL((attn_kernel<DD, MODE, W>), dim3((unsigned)nblocks), dim3(64 * W),         \
+                     (lds_bytes<DD, MODE, W>(pre)), s, a)
+  const int waves = a.hpw * a.ppw;
+  if (a.d == 128) {
+    if (waves == 8) DA_ATTN(128, 8);
+    else DA_ATTN(128, 4);
+  } else {
+    if (waves == 8) DA_ATTN(64, 8);
+    else DA_ATTN(64, 4);
+  }
+#undef DA_ATTN
   return hipGetLastError();
 }
 

@@ -1,0 +1,77 @@
+"""Both workgroup sizes of the attention kernels (eight wavefronts, and the four
+of small launches, short key sets and d = 64) on the same rows: bitwise equal
+to each other where one call can take either, and against the oracle."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from sampling import assert_parity, to_oracle_bits
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda"
+# with this max_seqlen the grid is past every small-launch rule, whatever the lengths are
+LONG = 1 << 18
+
+
+def B():
+    from paper_2505_11254_amd import binding
+    return binding
+
+
+def make(lens, Hq, Hkv, d, seed):
+    from paper_2505_11254_amd.inputs import random_qkv
+    return random_qkv(lens, Hq, Hkv, d, seed, device="cpu")
+
+
+# ragged lengths around a wavefront's 32 rows, the slabs of both sizes and a key tile
+LENS = [(1, 31, 33, 0, 63, 65, 127, 129, 255, 257, 700), (1500,)]
+
+
+@pytest.mark.parametrize("Hq,Hkv", [(2, 2), (4, 2), (6, 2), (4, 1), (8, 1)])
+@pytest.mark.parametrize("lens", LENS, ids=["ragged", "one"])
+def test_small_and_large_launches_agree_bitwise(lens, Hq, Hkv):
+    """Longer than 1024 keys per row, so that the block count alone decides."""
+    q, k, v, cu = (x.to(DEV) for x in make(lens, Hq, Hkv, 128, seed=Hq + len(lens)))
+    kw = dict(cu_seqlens=cu)
+    for fn, more in ((B().sparse_attn_prefill, dict(window=1100, n_sink=3)),
+                     (B().dense_causal_attn_prefill, {})):
+        small = fn(q, k, v, max_seqlen=max(lens), **kw, **more)
+        large = fn(q, k, v, max_seqlen=LONG, **kw, **more)
+        torch.cuda.synchronize()
+        assert torch.equal(small, large), fn.__name__
+
+
+# (lens, Hq, Hkv, d, window, n_sink, gamma, max_seqlen): fused slabs of half-size
+# workgroups with one, two and four heads, gammas that only a full-size slab holds
+# (256 at one head), many and few staged dense rows, odd gammas (unfused)
+DELTA = [
+    ((300, 1, 515), 1, 1, 64, 40, 3, 256, None),
+    ((700,), 2, 2, 64, 64, 4, 128, None),
+    ((900, 33), 8, 1, 64, 100, 5, 32, None),
+    ((700,), 4, 1, 64, 50, 0, 2, None),
+    ((515,), 5, 1, 64, 60, 1, 48, None),
+    ((700,), 4, 1, 128, 50, 0, 2, None),
+    ((700,), 4, 1, 128, 50, 0, 2, LONG),
+    ((600, 129), 4, 1, 128, 64, 4, 64, None),
+    ((600, 129), 4, 1, 128, 700, 4, 64, LONG),
+    ((515, 64), 3, 1, 128, 64, 4, 256, None),
+    ((515, 64), 3, 1, 128, 1200, 4, 256, LONG),
+    ((515,), 2, 1, 128, 60, 1, 7, None),
+]
+
+
+@pytest.mark.parametrize("case", DELTA, ids=[f"L{c[0]}-H{c[1]}/{c[2]}-d{c[3]}-w{c[4]}-g{c[6]}"
+                                             f"{'-long' if c[7] else ''}" for c in DELTA])
+def test_delta_matches_oracle_at_both_sizes(case):
+    lens, Hq, Hkv, d, w, s, gamma, max_seqlen = case
+    q, k, v, cu = make(lens, Hq, Hkv, d, seed=sum(lens) + d)
+    out = B().delta_attn_prefill(q.to(DEV), k.to(DEV), v.to(DEV), window=w, n_sink=s, gamma=gamma,
+                                 cu_seqlens=cu.to(DEV), max_seqlen=max_seqlen or max(lens))
+    torch.cuda.synchronize()
+    ref = oracle.delta_attention(*(to_oracle_bits(x) for x in (q, k, v)),
+                                 cu.numpy().astype(np.int64), window=w, n_sink=s, gamma=gamma)
+    assert_parity(out, ref, "delta path")
