@@ -14,6 +14,8 @@ namespace da {
 
 namespace {
 
+constexpr int kCUs = 256;  // of a gfx950
+
 thread_local int g_last_hip_error = 0;
 
 // Per-device answer to "is this a gfx950": 0 unknown, 1 yes, 2 no.
@@ -63,14 +65,41 @@ int fused_heads_per_block(int G, int gamma, int max_rows, int waves) {
   return 0;
 }
 
+// Key tiles all strided-row workgroups of kAttnWaves wavefronts run together:
+// row tiles of rpb rows, the anchors' growing with their position, those of
+// `tail` further rows reaching over the whole sequence.
+static int64_t strided_tiles(int64_t B, int64_t N, int Hq, int G, int64_t gamma, int64_t tail) {
+  const int hpw = heads_per_block(G);
+  const int64_t rpb = kRowsPerWave * (kAttnWaves / hpw);
+  const int64_t T = (N + kKeyTile - 1) / kKeyTile;
+  const int64_t nA = N / gamma, ra = (nA + rpb - 1) / rpb;
+  int64_t per = (int64_t)((double)ra * (ra + 1) / 2 * rpb * gamma / kKeyTile);
+  if (per > ra * T) per = ra * T;
+  per += ((nA + tail + rpb - 1) / rpb - ra) * T;
+  return B * (Hq / hpw) * per;
+}
+
 // Workspace of the Delta path.  Dense rows of a sequence of length L are the
 // floor(L/gamma) anchors plus the L mod gamma tail rows.  Their key axis is
-// split into nC chunks of `chunk` keys (at least 2560), up to 16 of them.
-// Workgroups that run at the same time then process one key chunk each in
-// step with their neighbours, which keeps them sharing that chunk's keys and
-// values in L2.  (The minimum sets nC only below 40960 keys.  At 32768, 13
+// split into nC chunks of `chunk` keys (at least kLongChunk tiles), up to 16 of
+// them.  Workgroups that run at the same time then process one key chunk each
+// in step with their neighbours, which keeps them sharing that chunk's keys
+// and values in L2.  (The minimum sets nC only below 40960 keys.  At 32768, 13
 // chunks of 2560 keys fill just under two rounds of the CUs where 16 of 2048
 // filled two and a quarter: 15 % less time on the strided rows and merge.)
+// Where chunks of that size leave CUs idle, shorter ones spread the rows over
+// the chip: as many tiles as give every CU one full-size workgroup's worth (two
+// half-size ones), at least kShortChunk.  In a batch the lengths may lie below
+// max_seqlen, so its chunks are half as long again shorter.  Measured on an
+// MI355X, Delta prefill, 2560-key minimum -> this: 32 heads d 128, 2048 tokens
+// 70.9 -> 45.2 us, 4021 tokens 168 -> 149 us, 8192 tokens 120 -> 106 us; 4
+// heads (one kv head) 8192 tokens 66.6 -> 42.1 us; 32 heads d 64 2048 tokens
+// 52.4 -> 32.7 us; eight packed prompts up to 3071 tokens 232 -> 223 us.  A
+// 4-tile minimum is no faster at d 128 (4021 tokens 158 us: the merge grows).
+// Twice as many chunks cost 5 % where the grid is full already (12000 tokens
+// 154 -> 166 us).  Sequences of at most 768 keys (1024 at d 64) keep one chunk,
+// which needs no merge: as fast there as two (d 128, 700 tokens 33-35 us, 1024
+// tokens 39-41 us against 37).
 // nC drops only when the partial results would pass 8 GiB, or, with a nonzero
 // `limit`, until the whole workspace fits `limit` bytes (false when even one
 // chunk does not).
@@ -80,8 +109,14 @@ bool make_plan(int B, int max_seqlen, int Hq, int Hkv, int d, int gamma, Plan* p
   if (Hq % Hkv != 0) return false;
   const int64_t nA_max = max_seqlen / gamma;
   const int64_t nR_max = nA_max + (int64_t)((gamma - 1 < max_seqlen) ? gamma - 1 : max_seqlen);
-  constexpr int64_t kMinChunkKeys = kKeyTile * 40;
-  int64_t nC = (max_seqlen + kMinChunkKeys - 1) / kMinChunkKeys;
+  constexpr int64_t kLongChunk = 40, kShortChunk = 8;  // tiles
+  const int64_t work = strided_tiles(B, max_seqlen, Hq, Hq / Hkv, gamma, nR_max - nA_max);
+  const int64_t places = B == 1 ? kCUs : kCUs * 3 / 2;
+  int64_t min_tiles = (work + places - 1) / places;
+  min_tiles = min_tiles < kShortChunk ? kShortChunk : min_tiles > kLongChunk ? kLongChunk : min_tiles;
+  const int64_t one = d == 64 ? 1024 : 768;  // keys
+  const int64_t min_keys = max_seqlen <= one ? one : kKeyTile * min_tiles;
+  int64_t nC = (max_seqlen + min_keys - 1) / min_keys;
   if (nC > 16) nC = 16;
   if (nC < 1) nC = 1;
   const int64_t per_chunk_bytes = (int64_t)B * Hq * nR_max * (d + 2) * 4;
@@ -155,7 +190,6 @@ da_status validate(const Problem& P, bool need_window, bool need_gamma) {
   return DA_OK;
 }
 
-constexpr int kCUs = 256;
 enum class Launch { kSparseRows, kDenseCausal, kStridedRows };
 
 // Wavefronts per attention workgroup: kAttnWaves, or half of them.  `blocks` is
@@ -244,20 +278,6 @@ void tile_dense(Args& a, const Problem& P) {
   int waves = attn_waves(Launch::kDenseCausal, P.d, h8, n_blocks(P, kAttnWaves, h8, P.N, 1), 0);
   if (n_blocks(P, waves, heads_per_block(G, waves), P.N, 1) > INT32_MAX) waves = kAttnWaves;
   set_tiling(a, waves, heads_per_block(G, waves), P.N);
-}
-
-// Key tiles all strided-row workgroups of kAttnWaves wavefronts run together:
-// row tiles of rpb rows, the anchors' growing with their position, those of
-// `tail` further rows reaching over the whole sequence.
-int64_t strided_tiles(int64_t B, int64_t N, int Hq, int G, int64_t gamma, int64_t tail) {
-  const int hpw = heads_per_block(G);
-  const int64_t rpb = kRowsPerWave * (kAttnWaves / hpw);
-  const int64_t T = (N + kKeyTile - 1) / kKeyTile;
-  const int64_t nA = N / gamma, ra = (nA + rpb - 1) / rpb;
-  int64_t per = (int64_t)((double)ra * (ra + 1) / 2 * rpb * gamma / kKeyTile);
-  if (per > ra * T) per = ra * T;
-  per += ((nA + tail + rpb - 1) / rpb - ra) * T;
-  return B * (Hq / hpw) * per;
 }
 
 // Tiles the strided dense rows: nR_max rows, nC chunks of `chunk` keys.
@@ -398,13 +418,22 @@ da_status run_delta(const Problem& P, void* workspace, size_t workspace_bytes, v
   if (fused) {
     a.dense = a.sa;
     a.fuse = corr_mode == DA_CORR_RECOMPUTE ? 2 : 1;
+    // One key chunk has nothing to merge: with both steps asked for, the strided
+    // kernel writes the dense rows themselves (the merge's arithmetic, one
+    // launch less: 1024 tokens, one d 64 head 32.5 -> 25.5 us).
+    const unsigned both = DA_STEP_DENSE_ROWS | DA_STEP_CORRECT;
+    const bool direct = plan.nC == 1 && (steps & both) == both;
     if (steps & DA_STEP_DENSE_ROWS) {
       Args ar = a;
       tile_strided(ar, P, plan);
+      if (direct) {
+        ar.part_o = a.dense;
+        ar.part_ml = nullptr;
+      }
       e = launch_dense_rows(ar, s);
       if (e != hipSuccess) return fail_hip(e);
     }
-    if (steps & DA_STEP_CORRECT) {
+    if ((steps & DA_STEP_CORRECT) && !direct) {
       e = launch_delta_epilogue(a, s);
       if (e != hipSuccess) return fail_hip(e);
     }

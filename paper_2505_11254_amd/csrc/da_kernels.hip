@@ -897,6 +897,11 @@ void attn_kernel(Args a) {
     float* const stg = (float*)smem + wave * (16 * D);
     const int rsub = lane / CPR, cc = lane % CPR;
     const int64_t row0 = ((int64_t)b * a.Hq + h) * a.nR_max;
+    if (!a.part_ml) {  // the only chunk: normalised rows, as the merge computes them
+      const float inv = 1.f / lt;
+#pragma unroll
+      for (int mb = 0; mb < D / 32; ++mb) o[mb] *= inv;
+    }
 #pragma unroll
     for (int pass = 0; pass < 2; ++pass) {
       if (pass) wave_lds_exchange();  // the first pass's reads are done
@@ -925,7 +930,7 @@ void attn_kernel(Args a) {
       for (int i = 0; i < NI; ++i)
         if (rb + i * RPI < R1) *(f32x4*)(prow + i * rstep) = w[i];
     }
-    if (row_valid && half == 0) {
+    if (a.part_ml && row_valid && half == 0) {
       const int64_t slot = (row0 + my_r) * a.nC + c;
       a.part_ml[slot * 2] = has_ref ? ref : -INFINITY;  // -inf when no key of the chunk is visible
       a.part_ml[slot * 2 + 1] = lt;

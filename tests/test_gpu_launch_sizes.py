@@ -75,3 +75,30 @@ def test_delta_matches_oracle_at_both_sizes(case):
     ref = oracle.delta_attention(*(to_oracle_bits(x) for x in (q, k, v)),
                                  cu.numpy().astype(np.int64), window=w, n_sink=s, gamma=gamma)
     assert_parity(out, ref, "delta path")
+
+
+# one key chunk (768 keys, 1024 at d 64) and the first sizes past it; chunks of the
+# shortest and of in-between lengths; a batch, whose chunks are shorter
+CHUNKS = [((n,), 4, 1, d) for d, edge in ((64, 1024), (128, 768)) for n in (1, 65, edge, edge + 1)] + \
+         [((2600,), 8, 8, 64), ((4021,), 2, 1, 128), ((1, 800, 1300), 4, 2, 128)]
+
+
+@pytest.mark.parametrize("lens,Hq,Hkv,d", CHUNKS, ids=[f"L{c[0]}-H{c[1]}/{c[2]}-d{c[3]}" for c in CHUNKS])
+def test_key_chunks_match_oracle_and_the_steps(lens, Hq, Hkv, d):
+    """The whole call (which skips the merge of a single chunk) equals its steps
+    one at a time bitwise, and the oracle."""
+    w, s, gamma = 40, 3, 32
+    q, k, v, cu = make(lens, Hq, Hkv, d, seed=sum(lens) + Hq)
+    qd, kd, vd, cud = (x.to(DEV) for x in (q, k, v, cu))
+    kw = dict(window=w, n_sink=s, gamma=gamma, cu_seqlens=cud, max_seqlen=max(lens))
+    out = B().delta_attn_prefill(qd, kd, vd, **kw)
+    ws = torch.empty(B().workspace_bytes(len(lens), max(lens), Hq, Hkv, d, gamma),
+                     dtype=torch.uint8, device=DEV)
+    by_steps = torch.empty_like(qd)
+    for st in (B().STEP_DENSE_ROWS, B().STEP_CORRECT, B().STEP_SPARSE):
+        B().delta_attn_prefill_steps(qd, kd, vd, by_steps, ws, st | B().STEP_FUSED, **kw)
+    torch.cuda.synchronize()
+    assert torch.equal(out, by_steps)
+    ref = oracle.delta_attention(*(to_oracle_bits(x) for x in (q, k, v)),
+                                 cu.numpy().astype(np.int64), window=w, n_sink=s, gamma=gamma)
+    assert_parity(out, ref, "delta path")
