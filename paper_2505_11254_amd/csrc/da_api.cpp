@@ -208,10 +208,10 @@ enum class Launch { kSparseRows, kDenseCausal, kStridedRows };
 //   d = 128, launches below one round of the CUs: dense 512-2048 tokens, 32
 //     heads 18.7 -> 14.3 and 52.1 -> 45.4 us, sparse 1K tokens 28.5 -> 23.8 us;
 //   d = 128, few keys per row (the fixed cost of a workgroup then outweighs its
-//     tiles), 32K tokens, 32 heads: window 64 200 -> 183 us, 256 275 -> 261 us,
-//     512 383 -> 377 us, 1024 593 -> 599 us; with 8 heads (one per workgroup,
-//     whose 256 rows reach further past the window) 1024 161 -> 156 us, 2048
-//     265 -> 268 us;
+//     tiles), 32K tokens, 32 heads, 64 sinks: window 64 200 -> 183 us, 256
+//     275 -> 261 us, 512 383 -> 377 us, 1024 593 -> 599 us; with 8 heads (one
+//     per workgroup, whose 256 rows reach further past the window) 1024
+//     161 -> 156 us, 1536 215 -> 214 us, 2048 265 -> 268 us;
 //   d = 128, a last round of at most half the CUs' places: 8 heads, window
 //     2048, 352 blocks 122 -> 106 us, 640 blocks 187 -> 172 us; but 256 blocks
 //     64.5 -> 68.6 us and 480 blocks 126 -> 133 us (whole rounds), and 32
@@ -220,7 +220,7 @@ int attn_waves(Launch kind, int d, int heads, int64_t blocks, int64_t keys) {
   constexpr int kHalf = kAttnWaves / 2;
   if (d == 64) return kHalf;
   if (kind == Launch::kSparseRows) {
-    if (keys <= (heads == 1 ? 1024 : 512)) return kHalf;
+    if (keys <= (heads == 1 ? 1600 : 600)) return kHalf;
     if (blocks < kCUs) return kHalf;
   } else if (blocks <= kCUs * 11 / 8) {
     // (workgroups of unequal length, longest first: 352 blocks of dense rows
