@@ -78,6 +78,7 @@ struct Args {
   // the launch's divisors: row tiles, key chunks, sequences, GQA group size
   // Hq / Hkv, gamma, query block
   FastDiv fd_rtiles, fd_nC, fd_B, fd_G, fd_gamma, fd_bq;
+  FastDiv fd_nR, fd_Hq;  // (merge)
   // Dense-row workgroup order when every sequence has the same length (set by
   // launch_dense_rows; dr_n1 = 0 keeps the plain order).  Row tiles
   // [dr_t[c], dr_nrt) take the whole of key chunk c, [dr_z[c], dr_t[c]) part

@@ -39,6 +39,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 enum Mode { kSparse = 0, kDense = 1, kDenseRows = 2 };
@@ -963,11 +964,68 @@ void attn_kernel(Args a) {
 // with key-block lists no anchor is assumed covered (cover = 0).
 // Epilogue modes: the Delta correction itself; "recompute" (Eq. 5: the dense
 // row replaces the sparse one at anchors only); merge only (Delta_i into
-// dbuf for the other correction variants, tail rows into out); or, for the
-// fused schedule, which runs before the sparse kernel, the merged dense rows
-// into a.dense in fp32 (covered anchors are skipped: their groups keep the
-// sparse rows).
-enum Epi { kEpiDelta = 0, kEpiRecompute = 1, kEpiMergeOnly = 2, kEpiMergeDense = 3 };
+// dbuf for the other correction variants, tail rows into out).
+enum Epi { kEpiDelta = 0, kEpiRecompute = 1, kEpiMergeOnly = 2 };
+
+// Log-sum-exp merge of the first nc key-chunk partials of one dense row:
+// values po[cc * D] (VF floats each) under (running max, normaliser) ml[cc].
+// One pass in chunk order with a running max M: chunks with no visible key
+// (max -inf) are skipped, and acc, lsum move to a larger M by 2^(M - Mn).
+// The loads of kU chunks go out before any of them is used.
+template <int D, typename VF>
+__device__ __forceinline__ VF merge_chunks(const float* po, const f32x2* ml, int nc) {
+  constexpr int kU = 8;
+  float M = -INFINITY, lsum = 0.f;
+  VF acc = VF{};
+  for (int c0 = 0; c0 < nc; c0 += kU) {
+    f32x2 m[kU];
+    VF x[kU];
+#pragma unroll
+    for (int j = 0; j < kU; ++j) {
+      const int cc = min(c0 + j, nc - 1);
+      m[j] = ml[cc];
+      x[j] = *(const VF*)(po + (int64_t)cc * D);
+    }
+#pragma unroll
+    for (int j = 0; j < kU; ++j) {
+      if (c0 + j >= nc || m[j][0] == -INFINITY) continue;
+      const float Mn = fmaxf(M, m[j][0]);
+      const float sc = fast_exp2(M - Mn), w = fast_exp2(m[j][0] - Mn);
+      lsum = lsum * sc + w * m[j][1];
+      acc = acc * sc + w * x[j];
+      M = Mn;
+    }
+  }
+  return acc * (1.f / lsum);
+}
+
+// The fused schedule's merge, ahead of the sparse kernel: the dense rows it
+// needs (tail rows and the anchors whose Delta is not zero) into a.dense in
+// fp32.  Bound by reading the partials; one thread per four values of a row
+// (a wavefront reads whole consecutive rows of one chunk stride), so that
+// even a short sequence's rows give every SIMD several wavefronts.
+template <int D>
+__global__ __launch_bounds__(kEpiThreads) void merge_dense_kernel(Args a) {
+  constexpr int V = D / 4;
+  const uint32_t n_rows = (uint32_t)a.B * (uint32_t)a.Hq * (uint32_t)a.nR_max;
+  constexpr uint32_t kRowsPerBlock = kEpiThreads / V;
+  for (uint32_t row = blockIdx.x * kRowsPerBlock + threadIdx.x / V; row < n_rows;
+       row += gridDim.x * kRowsPerBlock) {
+    const uint32_t bh = fdiv(row, a.fd_nR);
+    const int r = (int)(row - bh * (uint32_t)a.nR_max);
+    const int L = seq_of(a, (int)fdiv(bh, a.fd_Hq)).L;
+    const int nA = (int)fdiv((uint32_t)L, a.fd_gamma);
+    const int Lc = nA * a.gamma;
+    if (r >= nA + (L - Lc)) continue;
+    const int pos = r < nA ? r * a.gamma : Lc + (r - nA);
+    if (r < nA && (int64_t)pos < a.cover) continue;
+    const int nc = (int)(((int64_t)pos + a.chunk) / a.chunk);  // chunks holding keys 0..pos
+    const int dv = (int)(threadIdx.x % V) * 4;
+    const int64_t slot0 = (int64_t)row * a.nC;
+    *(f32x4*)(a.dense + (int64_t)row * D + dv) =
+        merge_chunks<D, f32x4>(a.part_o + slot0 * D + dv, (const f32x2*)a.part_ml + slot0, nc);
+  }
+}
 
 template <int D, int EPI>
 __global__ __launch_bounds__(kEpiThreads) void delta_epilogue_kernel(Args a) {
@@ -1009,28 +1067,8 @@ __global__ __launch_bounds__(kEpiThreads) void delta_epilogue_kernel(Args a) {
     const int hh = idx / DC, dc = idx % DC;
     const int h = h0 + hh;
     const int64_t slot0 = (((int64_t)b * a.Hq + h) * a.nR_max + r) * a.nC;
-    // one pass with a running max M (the loads of every chunk are independent,
-    // so they can all be in flight together): chunks with no visible key
-    // (max -inf) are skipped, and acc, lsum move to a larger M by 2^(M - Mn)
-    float M = -INFINITY, lsum = 0.f;
-    f32x8 acc = f32x8{};
-#pragma unroll 4
-    for (int cc = 0; cc < nc; ++cc) {
-      const float mc = a.part_ml[(slot0 + cc) * 2];
-      const float lc = a.part_ml[(slot0 + cc) * 2 + 1];
-      const f32x8 po = *(const f32x8*)(a.part_o + (slot0 + cc) * D + dc * 8);
-      if (mc == -INFINITY) continue;
-      const float Mn = fmaxf(M, mc);
-      const float sc = fast_exp2(M - Mn), w = fast_exp2(mc - Mn);
-      lsum = lsum * sc + w * lc;
-      acc = acc * sc + w * po;
-      M = Mn;
-    }
-    const f32x8 dense = acc * (1.f / lsum);
-    if (EPI == kEpiMergeDense) {
-      *(f32x8*)(a.dense + (((int64_t)b * a.Hq + h) * a.nR_max + r) * D + dc * 8) = dense;
-      continue;
-    }
+    const f32x8 dense =
+        merge_chunks<D, f32x8>(a.part_o + slot0 * D + dc * 8, (const f32x2*)a.part_ml + slot0, nc);
     uint16_t* orow = a.out + ((sq.base + pos) * a.Hq + h) * (int64_t)D + dc * 8;
     if (EPI != kEpiMergeOnly || !anchor) *(bf16x8_t*)orow = __builtin_convertvector(dense, bf16x8_t);
     if (anchor && EPI != kEpiRecompute) {
@@ -1351,25 +1389,39 @@ hipError_t launch_dense_rows(const Args& a0, hipStream_t s) {
   return launch_attn<kDenseRows>(a, s, (int64_t)a.B * a.n_hgroups * a.nC * a.n_rtiles);
 }
 
-hipError_t launch_delta_epilogue(const Args& a, hipStream_t s) {
+hipError_t launch_delta_epilogue(const Args& a0, hipStream_t s) {
+  const dim3 t(kEpiThreads);
+  if (a0.fuse) {
+    Args a = a0;
+    a.fd_nR = make_fastdiv((uint32_t)a.nR_max);
+    a.fd_Hq = make_fastdiv((uint32_t)a.Hq);
+    a.fd_gamma = make_fastdiv((uint32_t)a.gamma);
+    const int64_t rows = (int64_t)a.B * a.Hq * a.nR_max;
+    if (rows <= 0) return hipSuccess;
+    if (rows > INT32_MAX) return hipErrorInvalidValue;  // (over a terabyte of partials)
+    const int64_t rpb = kEpiThreads / (a.d / 4);
+    const dim3 g((unsigned)std::min<int64_t>((rows + rpb - 1) / rpb, 1 << 20));
+    if (a.d == 128)
+      hipLaunchKernelGGL(merge_dense_kernel<128>, g, t, 0, s, a);
+    else
+      hipLaunchKernelGGL(merge_dense_kernel<64>, g, t, 0, s, a);
+    return hipGetLastError();
+  }
+  const Args& a = a0;
   const int n_hc = (a.Hq + a.head_chunk - 1) / a.head_chunk;
   const int64_t nblocks = (int64_t)a.B * a.nR_max * n_hc;
   if (nblocks <= 0) return hipSuccess;
-  const dim3 g((unsigned)nblocks), t(kEpiThreads);
+  const dim3 g((unsigned)nblocks);
 #define DA_EPI(DD, E) hipLaunchKernelGGL((delta_epilogue_kernel<DD, E>), g, t, 0, s, a)
-  const int epi = a.fuse ? kEpiMergeDense
-                         : a.corr_mode == 0 ? kEpiDelta
-                         : a.corr_mode == 1 ? kEpiRecompute : kEpiMergeOnly;
+  const int epi = a.corr_mode == 0 ? kEpiDelta : a.corr_mode == 1 ? kEpiRecompute : kEpiMergeOnly;
   if (a.d == 128) {
     if (epi == kEpiDelta) DA_EPI(128, kEpiDelta);
     else if (epi == kEpiRecompute) DA_EPI(128, kEpiRecompute);
-    else if (epi == kEpiMergeOnly) DA_EPI(128, kEpiMergeOnly);
-    else DA_EPI(128, kEpiMergeDense);
+    else DA_EPI(128, kEpiMergeOnly);
   } else {
     if (epi == kEpiDelta) DA_EPI(64, kEpiDelta);
     else if (epi == kEpiRecompute) DA_EPI(64, kEpiRecompute);
-    else if (epi == kEpiMergeOnly) DA_EPI(64, kEpiMergeOnly);
-    else DA_EPI(64, kEpiMergeDense);
+    else DA_EPI(64, kEpiMergeOnly);
   }
 #undef DA_EPI
   return hipGetLastError();
