@@ -91,15 +91,16 @@ static int64_t strided_tiles(int64_t B, int64_t N, int Hq, int G, int64_t gamma,
 // the chip: as many tiles as give every CU one full-size workgroup's worth (two
 // half-size ones), at least kShortChunk.  In a batch the lengths may lie below
 // max_seqlen, so its chunks are half as long again shorter.  Measured on an
-// MI355X, Delta prefill, 2560-key minimum -> this: 32 heads d 128, 2048 tokens
-// 70.9 -> 45.2 us, 4021 tokens 168 -> 149 us, 8192 tokens 120 -> 106 us; 4
-// heads (one kv head) 8192 tokens 66.6 -> 42.1 us; 32 heads d 64 2048 tokens
-// 52.4 -> 32.7 us; eight packed prompts up to 3071 tokens 232 -> 223 us.  A
-// 4-tile minimum is no faster at d 128 (4021 tokens 158 us: the merge grows).
-// Twice as many chunks cost 5 % where the grid is full already (12000 tokens
-// 154 -> 166 us).  Sequences of at most 768 keys (1024 at d 64) keep one chunk,
-// which needs no merge: as fast there as two (d 128, 700 tokens 33-35 us, 1024
-// tokens 39-41 us against 37).
+// MI355X, Delta prefill, 2560-key minimum -> this: 32 heads d 128, 1024 tokens
+// 43.8 -> 27.5 us, 2048 tokens 70.9 -> 36 us, 4021 tokens 168 -> 139 us, 8192
+// tokens 120 -> 96 us; 32 heads d 64, 2048 tokens 52.4 -> 27.6 us; eight packed
+// prompts up to 3071 tokens 232 -> 212 us.  Against 2 tiles, a minimum of 4
+// takes 29.3 us at 1024 tokens and 8 takes 34.4 us; from 2048 tokens on 2 to 4
+// are alike.  Twice as many chunks cost 5 % where the grid is full already
+// (12000 tokens 154 -> 166 us).  Sequences of at most 448 keys keep one chunk,
+// which needs no merge (300 tokens 25.0 us against 26.7 us in two; 520 tokens
+// 30.8 us against 26.7 us), and so do up to 1024 keys of a problem of a single
+// workgroup.
 // nC drops only when the partial results would pass 8 GiB, or, with a nonzero
 // `limit`, until the whole workspace fits `limit` bytes (false when even one
 // chunk does not).
@@ -109,12 +110,14 @@ bool make_plan(int B, int max_seqlen, int Hq, int Hkv, int d, int gamma, Plan* p
   if (Hq % Hkv != 0) return false;
   const int64_t nA_max = max_seqlen / gamma;
   const int64_t nR_max = nA_max + (int64_t)((gamma - 1 < max_seqlen) ? gamma - 1 : max_seqlen);
-  constexpr int64_t kLongChunk = 40, kShortChunk = 8;  // tiles
+  constexpr int64_t kLongChunk = 40, kShortChunk = 2;  // tiles
   const int64_t work = strided_tiles(B, max_seqlen, Hq, Hq / Hkv, gamma, nR_max - nA_max);
   const int64_t places = B == 1 ? kCUs : kCUs * 3 / 2;
   int64_t min_tiles = (work + places - 1) / places;
   min_tiles = min_tiles < kShortChunk ? kShortChunk : min_tiles > kLongChunk ? kLongChunk : min_tiles;
-  const int64_t one = d == 64 ? 1024 : 768;  // keys
+  const int hpw = heads_per_block(Hq / Hkv);
+  const bool one_block = (int64_t)B * (Hq / hpw) == 1 && nR_max <= kRowsPerWave * (kAttnWaves / hpw);
+  const int64_t one = one_block ? 1024 : 448;  // keys
   const int64_t min_keys = max_seqlen <= one ? one : kKeyTile * min_tiles;
   int64_t nC = (max_seqlen + min_keys - 1) / min_keys;
   if (nC > 16) nC = 16;
@@ -420,7 +423,7 @@ da_status run_delta(const Problem& P, void* workspace, size_t workspace_bytes, v
     a.fuse = corr_mode == DA_CORR_RECOMPUTE ? 2 : 1;
     // One key chunk has nothing to merge: with both steps asked for, the strided
     // kernel writes the dense rows themselves (the merge's arithmetic, one
-    // launch less: 1024 tokens, one d 64 head 32.5 -> 25.5 us).
+    // launch less: 1024 tokens, one d 64 head 32.9 -> 29.5 us).
     const unsigned both = DA_STEP_DENSE_ROWS | DA_STEP_CORRECT;
     const bool direct = plan.nC == 1 && (steps & both) == both;
     if (steps & DA_STEP_DENSE_ROWS) {

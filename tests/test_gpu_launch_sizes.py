@@ -77,9 +77,9 @@ def test_delta_matches_oracle_at_both_sizes(case):
     assert_parity(out, ref, "delta path")
 
 
-# one key chunk (768 keys, 1024 at d 64) and the first sizes past it; chunks of the
-# shortest and of in-between lengths; a batch, whose chunks are shorter
-CHUNKS = [((n,), 4, 1, d) for d, edge in ((64, 1024), (128, 768)) for n in (1, 65, edge, edge + 1)] + \
+# one key chunk (448 keys, 1024 of a single workgroup) and the first sizes past it;
+# chunks of the shortest and of in-between lengths; a batch, whose chunks are shorter
+CHUNKS = [((n,), h, 1, d) for d in (64, 128) for n, h in ((1, 8), (448, 8), (449, 16), (1024, 1), (1025, 1))] + \
          [((2600,), 8, 8, 64), ((4021,), 2, 1, 128), ((1, 800, 1300), 4, 2, 128)]
 
 
