@@ -102,3 +102,25 @@ def test_key_chunks_match_oracle_and_the_steps(lens, Hq, Hkv, d):
     ref = oracle.delta_attention(*(to_oracle_bits(x) for x in (q, k, v)),
                                  cu.numpy().astype(np.int64), window=w, n_sink=s, gamma=gamma)
     assert_parity(out, ref, "delta path")
+
+
+@pytest.mark.parametrize("mode,params", [(2, (0.0, 0.0, 0.0)), (3, (0.05, 0.0, 0.0)), (3, (1.0, 0.0, 0.0)),
+                                         (4, (0.2, 5e-2, 3.5e-3)), (4, (0.05, 1.25e-4, 2.08e-5))])
+def test_recurrences_over_segment_edges_match_oracle(mode, params):
+    """The scan cuts a sequence's anchors into 64 segments: none, one and two
+    anchors, one per segment and around it, and several per segment with a
+    short last one (the last filter setting is the unstable one)."""
+    lens, gamma = (0, 1, 2, 4, 126, 128, 130, 133, 1900), 2
+    q, k, v, cu = make(lens, 2, 1, 64, seed=mode)
+    out = B().delta_attn_prefill_correction(
+        *(x.to(DEV) for x in (q, k, v)), window=9, n_sink=1, gamma=gamma, mode=mode,
+        params=params, cu_seqlens=cu.to(DEV), max_seqlen=max(lens))
+    torch.cuda.synchronize()
+    ref = oracle.delta_attention_variant(*(to_oracle_bits(x) for x in (q, k, v)),
+                                         cu.numpy().astype(np.int64), window=9, n_sink=1,
+                                         gamma=gamma, mode=mode, params=params)
+    # (a window of 9 keys leaves outputs of O(1): their bf16 rounding, twice in this
+    # schedule, comes on top of the parity bound)
+    err = np.abs(out.float().cpu().numpy().astype(np.float64) - ref)
+    assert (err <= 2e-2 + 2 * np.abs(ref) * 2.0 ** -8).all(), err.max()
+    assert err.mean() <= 2e-3 + np.abs(ref).mean() * 2.0 ** -8
