@@ -1051,7 +1051,7 @@ __global__ __launch_bounds__(kEpiThreads) void merge_rows_kernel(Args a) {
 
 template <int D, int EPI>
 __global__ __launch_bounds__(kEpiThreads) void delta_epilogue_kernel(Args a) {
-  __shared__ float delta[8192];  // [head in range][D]
+  extern __shared__ __attribute__((aligned(16))) float delta[];  // [head in range][D]
   const int tid = threadIdx.x;
   int64_t lid = blockIdx.x;
   const int n_hc = (a.Hq + a.head_chunk - 1) / a.head_chunk;
@@ -1272,8 +1272,8 @@ __global__ __launch_bounds__(kScanCh * kScanSegs) void corr_scan_kernel(Args a) 
 // q^(k+1) Ein_i + (1 - q^(k+1)) Delta_i; filter: the filtered Delta_i.
 template <int D, int CORR>
 __global__ __launch_bounds__(kEpiThreads) void corr_apply_kernel(Args a) {
-  __shared__ float c0[8192];
-  __shared__ float c1[8192];
+  extern __shared__ __attribute__((aligned(16))) float c0[];  // [head in range][D], twice
+  float* const c1 = c0 + a.head_chunk * D;
   const int tid = threadIdx.x;
   int64_t lid = blockIdx.x;
   const int n_hc = (a.Hq + a.head_chunk - 1) / a.head_chunk;
@@ -1484,6 +1484,21 @@ hipError_t launch_dense_rows(const Args& a0, hipStream_t s) {
   return launch_attn<kDenseRows>(a, s, (int64_t)a.B * a.n_hgroups * a.nC * a.n_rtiles);
 }
 
+// Query heads per workgroup of the in-place passes over `out`: a.head_chunk, or
+// fewer where that leaves under eight workgroups per CU and each still has 16
+// vectors per thread.  Measured on an MI355X, all heads -> this: Delta, 16 heads
+// d 128, gamma 100, 1000 tokens 57.8 -> 39.2 us, 5000 tokens 90 -> 71 us;
+// interpolation 32 heads, 5376 tokens, gamma 64 125 -> 103 us; GQA 3, 20K tokens,
+// gamma 48, the epilogue alone 51 -> 46 us.  Without the second condition gamma 7
+// loses: 16 heads d 64, 5000 tokens 55.7 -> 59.6 us.
+int epilogue_heads(const Args& a, int64_t rows) {
+  int hc = std::min(a.head_chunk, a.Hq);
+  while (hc > 4 && a.B * rows * ((a.Hq + hc - 1) / hc) < 8 * 256 &&
+         (int64_t)a.gamma * hc * (a.d / 8) >= 2 * 16 * kEpiThreads)
+    hc = (hc + 1) / 2;
+  return hc;
+}
+
 hipError_t launch_delta_epilogue(const Args& a0, hipStream_t s) {
   const dim3 t(kEpiThreads);
   if (a0.fuse || a0.corr_mode >= 2) {
@@ -1505,12 +1520,14 @@ hipError_t launch_delta_epilogue(const Args& a0, hipStream_t s) {
     }
     return hipGetLastError();
   }
-  const Args& a = a0;
+  Args a = a0;
+  a.head_chunk = epilogue_heads(a, a.nR_max);
+  const unsigned lds = (unsigned)(a.head_chunk * a.d * 4);
   const int n_hc = (a.Hq + a.head_chunk - 1) / a.head_chunk;
   const int64_t nblocks = (int64_t)a.B * a.nR_max * n_hc;
   if (nblocks <= 0) return hipSuccess;
   const dim3 g((unsigned)nblocks);
-#define DA_EPI(DD, E) hipLaunchKernelGGL((delta_epilogue_kernel<DD, E>), g, t, 0, s, a)
+#define DA_EPI(DD, E) hipLaunchKernelGGL((delta_epilogue_kernel<DD, E>), g, t, lds, s, a)
   if (a.d == 128) {
     if (a.corr_mode == 0) DA_EPI(128, kEpiDelta);
     else DA_EPI(128, kEpiRecompute);
@@ -1524,7 +1541,8 @@ hipError_t launch_delta_epilogue(const Args& a0, hipStream_t s) {
 
 // After the merge: the scan (EMA, filter) and the apply pass of
 // the smoothing variants (modes 2-4).
-hipError_t launch_correction(const Args& a, hipStream_t s) {
+hipError_t launch_correction(const Args& a0, hipStream_t s) {
+  Args a = a0;
   if (a.corr_mode < 2) return hipSuccess;
   if (a.corr_mode >= 3) {
     const dim3 g((unsigned)((int64_t)a.B * a.Hq * a.d / kScanCh)), t(kScanCh * kScanSegs);
@@ -1535,11 +1553,13 @@ hipError_t launch_correction(const Args& a, hipStream_t s) {
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
+  a.head_chunk = epilogue_heads(a, a.nA_max);
+  const unsigned lds = (unsigned)(2 * a.head_chunk * a.d * 4);
   const int n_hc = (a.Hq + a.head_chunk - 1) / a.head_chunk;
   const int64_t nblocks = (int64_t)a.B * a.nA_max * n_hc;
   if (nblocks <= 0) return hipSuccess;
   const dim3 g((unsigned)nblocks), t(kEpiThreads);
-#define DA_APPLY(DD, C) hipLaunchKernelGGL((corr_apply_kernel<DD, C>), g, t, 0, s, a)
+#define DA_APPLY(DD, C) hipLaunchKernelGGL((corr_apply_kernel<DD, C>), g, t, lds, s, a)
   if (a.d == 128) {
     if (a.corr_mode == 2) DA_APPLY(128, 2);
     else if (a.corr_mode == 3) DA_APPLY(128, 3);
