@@ -194,11 +194,14 @@ da_status validate(const Problem& P, bool need_window, bool need_gamma) {
 }
 
 enum class Launch { kSparseRows, kDenseCausal, kStridedRows };
+constexpr int64_t kListKeys = 2048;  // keys of a row under key-block lists, as a typical guess
 
 // Wavefronts per attention workgroup: kAttnWaves, or half of them.  `blocks` is
-// the launch in 8-wave workgroups (equivalents of the longest one), `keys` the
-// keys of a sparse row.  Outputs are bitwise the same either way: a wavefront
-// runs the same rows over the same tiles.
+// the launch in 8-wave workgroups, `work` its tiles in units of the longest of
+// them, `keys` the keys of a sparse row, `even` whether nearly all workgroups
+// are that long.  Outputs
+// are bitwise the same either way: a wavefront runs the same rows over the same
+// tiles.
 //
 // Half-size workgroups fit a CU twice at d = 128 (registers: one wavefront per
 // SIMD each), so that one's first loads and last stores run beside the other's
@@ -208,35 +211,37 @@ enum class Launch { kSparseRows, kDenseCausal, kStridedRows };
 // always pays.  Measured on an MI355X, 8 -> 4 wavefronts:
 //   d = 64: 16-head sparse rows, window 1024, 38K tokens 282 -> 223 us; Delta
 //     prefill 131K tokens, 32 heads 6.01 -> 5.34 ms; dense 16K 1.16 -> 1.06 ms;
-//   d = 128, launches below one round of the CUs: dense 512-2048 tokens, 32
-//     heads 18.7 -> 14.3 and 52.1 -> 45.4 us, sparse 1K tokens 28.5 -> 23.8 us;
+//   d = 128, less work than the CUs hold: dense 512-2048 tokens, 32 heads
+//     18.7 -> 14.3 and 52.1 -> 45.4 us, 3000 tokens 78.2 -> 75.5 us (0.73
+//     rounds of the CUs), 4096 tokens 123 -> 134 us (1.0); sparse, window 2048,
+//     2500 tokens 74.6 -> 69.5 us (0.7), 3000 tokens 88 -> 95 us (0.95);
 //   d = 128, few keys per row (the fixed cost of a workgroup then outweighs its
 //     tiles), 32K tokens, 32 heads, 64 sinks: window 64 200 -> 183 us, 256
 //     275 -> 261 us, 512 383 -> 377 us, 1024 593 -> 599 us; with 8 heads (one
 //     per workgroup, whose 256 rows reach further past the window) 1024
 //     161 -> 156 us, 1536 215 -> 214 us, 2048 265 -> 268 us;
-//   d = 128, a last round of at most half the CUs' places: 8 heads, window
-//     2048, 352 blocks 122 -> 106 us, 640 blocks 187 -> 172 us; but 256 blocks
-//     64.5 -> 68.6 us and 480 blocks 126 -> 133 us (whole rounds), and 32
-//     heads, 2080 blocks 513 -> 525 us.
-int attn_waves(Launch kind, int d, int heads, int64_t blocks, int64_t keys) {
+//   d = 128, window 2048, a few rounds of the CUs: where the last round leaves
+//     many places, half-size workgroups share them better.  Uneven workgroups
+//     (32 heads, whole call, rounds by work): 4021 tokens 135.7 -> 128.4 us
+//     (1.46), 6000 tokens 201 -> 196 us (2.42), but 3500 tokens 111 -> 114 us
+//     (1.2), 5000 tokens 153 -> 160 us (1.95).  Even ones (8 heads, rounds by
+//     workgroups): 11264 tokens 120 -> 106 us (1.4), 13312 121 -> 110 us (1.6),
+//     17408 150 -> 144 us (2.1), but 8192 63 -> 69 us (1.0), 15360 126 -> 132 us
+//     (1.9);
+//   d = 128, strided rows up to 1.4 rounds: 16384 tokens, gamma 64 220 -> 211 us
+//     (0.8), 8 heads, gamma 32, 32768 tokens 208 -> 188 us (1.0); past it even
+//     workgroups, of which half a round may be left: 64 heads, gamma 32, 14848
+//     tokens 314 -> 322 us (1.53), 32 heads, 49945 tokens 1314 -> 1334 us (3.7).
+int attn_waves(Launch kind, int d, int heads, int64_t blocks, int64_t work, int64_t keys,
+               bool even) {
   constexpr int kHalf = kAttnWaves / 2;
   if (d == 64) return kHalf;
-  if (kind == Launch::kSparseRows) {
-    if (keys <= (heads == 1 ? 1600 : 600)) return kHalf;
-    if (blocks < kCUs) return kHalf;
-  } else if (blocks <= kCUs * 11 / 8) {
-    // (workgroups of unequal length, longest first: 352 blocks of dense rows
-    // 75.8 -> 67.8 us, 416 blocks 90.7 -> 94.7 us)
-    return kHalf;
-  }
-  if (blocks > 4 * kCUs || kind == Launch::kDenseCausal) return kAttnWaves;
-  // Rounds in hundredths: a half-size workgroup alone on its CU takes about 0.6
-  // of the time that two take together, and a full round 4 % longer.
-  const int64_t rest = 2 * blocks % (2 * kCUs);
-  const int64_t r8 = (blocks + kCUs - 1) / kCUs * 100;
-  const int64_t r4 = 2 * blocks / (2 * kCUs) * 104 + (rest == 0 ? 0 : rest <= kCUs ? 62 : 104);
-  return r4 < r8 ? kHalf : kAttnWaves;
+  if (kind == Launch::kSparseRows && keys <= (heads == 1 ? 1600 : 600)) return kHalf;
+  if (work * 5 < kCUs * 4 || (kind == Launch::kStridedRows && work <= kCUs * 11 / 8)) return kHalf;
+  if (work > 4 * kCUs || kind == Launch::kDenseCausal) return kAttnWaves;
+  const int64_t part = (even ? blocks : work) % kCUs * 100 / kCUs;  // of a round, in hundredths
+  const int64_t least = even ? 1 : 28, most = kind == Launch::kStridedRows ? 50 : 72;
+  return part >= least && part <= most ? kHalf : kAttnWaves;
 }
 
 // Tiling of a launch over `rows` rows per (sequence, head) by workgroups of
@@ -264,8 +269,12 @@ void tile_sparse(Args& a, const Problem& P, bool fused) {
     return fused ? fused_heads_per_block(G, P.gamma, max_rows, waves) : heads_per_block(G, waves);
   };
   const int h8 = heads(kAttnWaves);
-  const int64_t keys = P.blk_ptr ? INT64_MAX : (int64_t)P.window + P.n_sink;
-  int waves = attn_waves(Launch::kSparseRows, P.d, h8, n_blocks(P, kAttnWaves, h8, P.N, 1), keys);
+  const int64_t keys = P.blk_ptr ? kListKeys : (int64_t)P.window + P.n_sink;
+  // rows before a whole key set grow with their position
+  const int64_t blocks = n_blocks(P, kAttnWaves, h8, P.N, 1);
+  const int64_t ramp = keys < P.N ? keys : P.N;
+  const int64_t work = blocks * (2 * (int64_t)P.N - ramp) / (2 * (int64_t)P.N);
+  int waves = attn_waves(Launch::kSparseRows, P.d, h8, blocks, work, keys, P.N >= 4 * keys);
   // (a slab of half the rows may hold no whole group, and twice the blocks may
   // pass the grid's limit)
   if (waves < kAttnWaves &&
@@ -278,7 +287,8 @@ void tile_sparse(Args& a, const Problem& P, bool fused) {
 void tile_dense(Args& a, const Problem& P) {
   const int G = P.Hq / P.Hkv;
   const int h8 = heads_per_block(G);
-  int waves = attn_waves(Launch::kDenseCausal, P.d, h8, n_blocks(P, kAttnWaves, h8, P.N, 1), 0);
+  const int64_t work = n_blocks(P, kAttnWaves, h8, P.N, 1) / 2;
+  int waves = attn_waves(Launch::kDenseCausal, P.d, h8, 2 * work, work, 0, false);
   if (n_blocks(P, waves, heads_per_block(G, waves), P.N, 1) > INT32_MAX) waves = kAttnWaves;
   set_tiling(a, waves, heads_per_block(G, waves), P.N);
 }
@@ -287,9 +297,8 @@ void tile_dense(Args& a, const Problem& P) {
 void tile_strided(Args& a, const Problem& P, const Plan& plan) {
   const int G = P.Hq / P.Hkv;
   const int64_t tail = P.cu ? (int64_t)plan.nR_max - plan.nA_max : P.N % P.gamma;
-  const int64_t work = strided_tiles(P.B, P.N, P.Hq, G, P.gamma, tail);
-  int waves = attn_waves(Launch::kStridedRows, P.d, heads_per_block(G),
-                         work / (plan.chunk / kKeyTile), 0);
+  const int64_t work = strided_tiles(P.B, P.N, P.Hq, G, P.gamma, tail) / (plan.chunk / kKeyTile);
+  int waves = attn_waves(Launch::kStridedRows, P.d, heads_per_block(G), work, work, 0, true);
   if (n_blocks(P, waves, heads_per_block(G, waves), plan.nR_max, plan.nC) > INT32_MAX)
     waves = kAttnWaves;
   set_tiling(a, waves, heads_per_block(G, waves), plan.nR_max);

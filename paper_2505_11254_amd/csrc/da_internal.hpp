@@ -79,6 +79,11 @@ struct Args {
   // Hq / Hkv, gamma, query block
   FastDiv fd_rtiles, fd_nC, fd_B, fd_G, fd_gamma, fd_bq;
   FastDiv fd_nR, fd_Hq;  // (merge)
+  // block order, set by the launcher: n_sub head groups innermost, the s-th of
+  // them the head group (s % turn) * turn_step + s / turn
+  int n_sub, turn, turn_step;
+  FastDiv fd_sub, fd_turn;
+  int xcd_log;        // log2 of the logical blocks an XCD takes in a row (set by the launcher)
   // Dense-row workgroup order when every sequence has the same length (set by
   // launch_dense_rows; dr_n1 = 0 keeps the plain order).  Row tiles
   // [dr_t[c], dr_nrt) take the whole of key chunk c, [dr_z[c], dr_t[c]) part

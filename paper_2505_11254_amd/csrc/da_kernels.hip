@@ -82,27 +82,42 @@ __device__ __forceinline__ Seq seq_of(const Args& a, int b) {
 }
 
 // Workgroups are dispatched in order, round-robin over the 8 XCDs (block i ->
-// XCD i % 8), each with its own L2.  Logical blocks are ordered head group
-// outermost, then sequence, [key chunk,] row tile.
+// XCD i % 8), each with its own L2.
 //  - When the head groups split evenly over the XCDs, XCD x takes the
-//    contiguous eighth [x*n/8, (x+1)*n/8): whole head groups, each with every
-//    sequence, so the XCDs get equal work and each streams its own kv heads'
-//    keys and values through its L2 while neighbouring tiles share them.
-//  - Otherwise XCD x takes the logical chunks x, x+8, x+16, ... of kXcdChunk
-//    consecutive blocks: neighbouring tiles still run together on one L2,
-//    and all XCDs walk the logical order at the same pace, which spreads
-//    uneven work (sequences of different lengths, triangular key ranges).
-//    Blocks past the last whole round of 8 chunks keep their index.
-constexpr int kXcdChunk = 64;
-__device__ __forceinline__ uint32_t xcd_remap(uint32_t i, uint32_t n, bool contiguous) {
+//    contiguous eighth [x*n/8, (x+1)*n/8) of the logical blocks, ordered head
+//    groups outermost, then sequence, [key chunk,] row tile: whole head groups,
+//    each with every sequence, so the XCDs get equal work and each streams its
+//    own kv heads' keys and values through its L2 while neighbouring tiles
+//    share them.  Where an eighth is whole kv heads, the head groups of one kv
+//    head run innermost: the workgroups that read the same keys and values run
+//    side by side.
+//  - Otherwise all head groups run innermost, the kv heads in turn, so that
+//    the round-robin keeps as few kv heads per XCD as their number allows, the
+//    XCDs get equal work and the longest rows of all heads run first.  Against
+//    chunks of 64 blocks per XCD, head groups outermost, in every mode, which
+//    left XCDs idle where few blocks had work: dense causal, d 128, 32 heads on
+//    4 kv heads, 16K tokens 2541 -> 1807 us, 20 on 4 1269 -> 1113 us; Delta, 8
+//    heads on 4, packed prompts 4-22K tokens 445 -> 319 us; 8 heads on 2, 64K
+//    tokens 771 -> 681 us.
+//  - Sparse rows whose head groups are so few that the round-robin would put
+//    kXcdSpread rows or more between an XCD's neighbouring slabs: XCD x takes the
+//    logical chunks x, x+8, x+16, ... of `chunk` consecutive blocks, so that
+//    slabs whose windows overlap stay on one L2 (4 heads on 4, window 1000, 100K
+//    tokens, whole call 508 -> 463 us; 16 heads on 4, 128 rows apart, 477 us
+//    without and 489 us with it).  The chunk (a power of two, at most kXcdChunk)
+//    leaves at least four rounds of chunks; blocks past the last whole round of 8
+//    chunks keep their index.
+constexpr int kXcdChunk = 64, kXcdSpread = 256;
+__device__ __forceinline__ uint32_t xcd_remap(uint32_t i, uint32_t n, bool contiguous,
+                                              int log_chunk) {
   if (contiguous) {
     const uint32_t per = n / 8;
     return i < per * 8 ? (i % 8) * per + i / 8 : i;
   }
-  const uint32_t span = 8 * kXcdChunk;
+  const uint32_t span = 8u << log_chunk;
   if (i >= n / span * span) return i;
   const uint32_t k = i / 8;
-  return ((i % 8) + 8 * (k / kXcdChunk)) * kXcdChunk + k % kXcdChunk;
+  return (((i % 8) + 8 * (k >> log_chunk)) << log_chunk) + (k & ((1u << log_chunk) - 1));
 }
 
 __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
@@ -222,8 +237,11 @@ void attn_kernel(Args a) {
 
   // ---- which (sequence, head group, row tile[, key chunk]) this block owns
   // (grids hold fewer than 2^31 blocks; the divisors are the launch's)
-  uint32_t lid = xcd_remap(blockIdx.x, gridDim.x, a.n_hgroups % 8 == 0);
-  uint32_t q = fdiv(lid, a.fd_rtiles);
+  uint32_t lid = xcd_remap(blockIdx.x, gridDim.x, a.n_hgroups % 8 == 0, a.xcd_log);
+  uint32_t q = fdiv(lid, a.fd_sub);
+  const uint32_t sub_hg = lid - q * (uint32_t)a.n_sub;
+  lid = q;
+  q = fdiv(lid, a.fd_rtiles);
   int rt = (int)(lid - q * (uint32_t)a.n_rtiles);
   lid = q;
   int c = 0;
@@ -232,8 +250,11 @@ void attn_kernel(Args a) {
     c = (int)(lid - q * (uint32_t)a.nC);
     lid = q;
   }
-  const int hg = (int)fdiv(lid, a.fd_B);
-  const int b = (int)(lid - (uint32_t)hg * (uint32_t)a.B);
+  q = fdiv(lid, a.fd_B);
+  const int b = (int)(lid - q * (uint32_t)a.B);
+  // (sub_hg counts the kv heads in turn where all head groups run innermost)
+  const uint32_t turn = fdiv(sub_hg, a.fd_turn);
+  const int hg = (int)(q * (uint32_t)a.n_sub + (sub_hg - turn * (uint32_t)a.turn) * (uint32_t)a.turn_step + turn);
   // Longest rows first.  In the dense modes blocks dispatched together then have
   // (nearly) the same number of key tiles, start on the same tile and stay in
   // step, so they share each key/value tile in L2.  In the sparse mode the rows
@@ -1389,6 +1410,22 @@ hipError_t launch_attn(const Args& a0, hipStream_t s, int64_t nblocks) {
   a.fd_G = make_fastdiv((uint32_t)(a.Hq / a.Hkv));
   a.fd_gamma = make_fastdiv((uint32_t)a.gamma);
   a.fd_bq = make_fastdiv((uint32_t)(a.block_q > 0 ? a.block_q : 1));
+  const int per_kv = a.Hq / a.Hkv / a.hpw;
+  if (a.n_hgroups % 8 == 0) {
+    // (an eighth that is half a kv head would be its shorter or longer rows)
+    a.n_sub = a.Hkv % 8 == 0 ? per_kv : 1;
+    a.turn = a.n_sub;
+    a.turn_step = 1;
+  } else {
+    a.n_sub = a.n_hgroups;
+    a.turn = a.Hkv;
+    a.turn_step = per_kv;
+  }
+  a.fd_sub = make_fastdiv((uint32_t)a.n_sub);
+  a.fd_turn = make_fastdiv((uint32_t)a.turn);
+  a.xcd_log = 0;
+  if (MODE == kSparse && kRowsPerWave * a.ppw * 8 >= kXcdSpread * a.n_hgroups)
+    while ((2 << a.xcd_log) <= kXcdChunk && nblocks >= ((int64_t)4 * 8 * 2 << a.xcd_log)) ++a.xcd_log;
   // dense rows a sparse workgroup stages for the fused store
   const int pre = MODE == kSparse && a.fuse && a.gamma > 1
                       ? a.hpw * (kRowsPerWave * a.ppw / a.gamma) * a.d * 4 : 0;

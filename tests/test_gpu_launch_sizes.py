@@ -124,3 +124,27 @@ def test_recurrences_over_segment_edges_match_oracle(mode, params):
     err = np.abs(out.float().cpu().numpy().astype(np.float64) - ref)
     assert (err <= 2e-2 + 2 * np.abs(ref) * 2.0 ** -8).all(), err.max()
     assert err.mean() <= 2e-3 + np.abs(ref).mean() * 2.0 ** -8
+
+
+@pytest.mark.parametrize("Hkv", [1, 2, 3, 4, 5, 8, 10, 12, 16])
+@pytest.mark.parametrize("G", [1, 2, 3, 4, 5, 8])
+def test_block_order_covers_every_head_and_row(Hkv, G):
+    """Each kv head's group in a call of its own (another number of head groups,
+    so another block order) gives the same bits, for all three kernels (at most
+    448 keys: one key chunk whatever the heads are)."""
+    lens, d, window, n_sink, gamma = (430, 1, 137), 64 if G % 2 else 128, 30, 2, 32
+    q, k, v, cu = (x.to(DEV) for x in make(lens, Hkv * G, Hkv, d, seed=Hkv * 10 + G))
+    kw = dict(cu_seqlens=cu, max_seqlen=max(lens))
+
+    def all_three(q, k, v):
+        return (B().sparse_attn_prefill(q, k, v, window=window, n_sink=n_sink, **kw),
+                B().dense_causal_attn_prefill(q, k, v, **kw),
+                B().delta_attn_prefill(q, k, v, window=window, n_sink=n_sink, gamma=gamma, **kw))
+
+    whole = all_three(q, k, v)
+    for h in range(Hkv):
+        one = all_three(q[:, h * G:(h + 1) * G].contiguous(), k[:, h:h + 1].contiguous(),
+                        v[:, h:h + 1].contiguous())
+        torch.cuda.synchronize()
+        for name, x, y in zip(("sparse", "dense", "delta"), whole, one):
+            assert torch.equal(x[:, h * G:(h + 1) * G], y), (name, h)
