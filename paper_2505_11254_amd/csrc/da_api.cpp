@@ -283,6 +283,9 @@ void tile_sparse(Args& a, const Problem& P, bool fused) {
   set_tiling(a, waves, heads(waves), P.N);
 }
 
+int64_t sparse_blocks(const Args& a) { return (int64_t)a.B * a.n_hgroups * a.n_rtiles; }
+int64_t strided_blocks(const Args& a) { return sparse_blocks(a) * a.nC; }
+
 // Tiles the dense causal launch.
 void tile_dense(Args& a, const Problem& P) {
   const int G = P.Hq / P.Hkv;
@@ -457,17 +460,23 @@ da_status run_delta(const Problem& P, void* workspace, size_t workspace_bytes, v
     }
     return DA_OK;
   }
+  Args as = a, ar = a;
+  tile_sparse(as, P, false);
+  tile_strided(ar, P, plan);
+  const unsigned both = DA_STEP_SPARSE | DA_STEP_DENSE_ROWS;
+  // one launch for both, up to 40 rounds of the CUs (where it pays: see
+  // attn_pair_kernel) and where they take workgroups of one size
+  const bool pair = (steps & both) == both && as.hpw * as.ppw == ar.hpw * ar.ppw &&
+                    sparse_blocks(as) * as.hpw * as.ppw <= 40 * kCUs * kAttnWaves &&
+                    strided_blocks(ar) < INT32_MAX / 2;
+  if (pair) as.rows = &ar;
   // Step 1: sparse attention for every row (+ fp32 copy at anchors).
   if (steps & DA_STEP_SPARSE) {
-    Args as = a;
-    tile_sparse(as, P, false);
     e = launch_sparse(as, s);
     if (e != hipSuccess) return fail_hip(e);
   }
   // Steps 2-3: dense attention at anchors and tail rows, key axis split in chunks.
-  if (steps & DA_STEP_DENSE_ROWS) {
-    Args ar = a;
-    tile_strided(ar, P, plan);
+  if ((steps & DA_STEP_DENSE_ROWS) && !pair) {
     e = launch_dense_rows(ar, s);
     if (e != hipSuccess) return fail_hip(e);
   }

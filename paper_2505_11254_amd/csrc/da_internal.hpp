@@ -111,6 +111,10 @@ struct Args {
   float* dbuf;        // [B][Hq][nA_max][d]  Delta_i (filtered in place by the filter mode)
   float* ebuf;        // [B][Hq][nA_max][d]  EMA value entering group i
 
+  // Host side only: launch_sparse launches these strided rows (as launch_dense_rows
+  // would) together with the sparse rows, in workgroups of as many wavefronts.
+  const Args* rows;
+
   // Fused schedule: the sparse kernel stores the corrected rows itself from the
   // merged dense rows (0: plain sparse store; 1: Delta correction; 2: recompute).
   int fuse;

@@ -215,9 +215,9 @@ constexpr int lds_bytes(int pre_bytes) {
          (MODE == kSparse ? pre_bytes + (NW > 4 ? (NW - 4) * kRowsPerWave * D * 2 : 0) : 0);
 }
 
+// One attention workgroup, block `bid` of the launch's `nblk`.
 template <int D, int MODE, int NW>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 64 && NW == 4 ? 3 : 2)))
-void attn_kernel(Args a) {
+__device__ __forceinline__ void attn_body(const Args& a, uint32_t bid, uint32_t nblk) {
   using LD = Lds<D, NW>;
   constexpr int NS = kAttnStages;
   constexpr int kThreads = 64 * NW;
@@ -237,7 +237,7 @@ void attn_kernel(Args a) {
 
   // ---- which (sequence, head group, row tile[, key chunk]) this block owns
   // (grids hold fewer than 2^31 blocks; the divisors are the launch's)
-  uint32_t lid = xcd_remap(blockIdx.x, gridDim.x, a.n_hgroups % 8 == 0, a.xcd_log);
+  uint32_t lid = xcd_remap(bid, nblk, a.n_hgroups % 8 == 0, a.xcd_log);
   uint32_t q = fdiv(lid, a.fd_sub);
   const uint32_t sub_hg = lid - q * (uint32_t)a.n_sub;
   lid = q;
@@ -978,6 +978,32 @@ void attn_kernel(Args a) {
   }
 }
 
+#define DA_ATTN_KERNEL(D, NW) \
+  __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 64 && NW == 4 ? 3 : 2)))
+
+template <int D, int MODE, int NW>
+DA_ATTN_KERNEL(D, NW) void attn_kernel(Args a) {
+  attn_body<D, MODE, NW>(a, blockIdx.x, gridDim.x);
+}
+
+// The strided dense rows (`ar`, the first nr blocks: longer ones) and the sparse
+// rows (`as`, from block nr8 on, nr rounded up to the XCDs' turn) of the unfused
+// schedule, which do not depend on each other, in one launch: the sparse
+// workgroups fill the CUs that the last strided ones leave, and a short call
+// waits for the longer of the two instead of both.  Measured on an MI355X, two
+// launches -> one, whole calls: interpolation, 32 heads d 128, window 512, 500
+// tokens 36.0 -> 27.5 us, 4000 tokens 89 -> 77 us, 16000 tokens 302 -> 279 us;
+// Delta, GQA 3, gamma 48, 20K tokens 433 -> 402 us; EMA 64K tokens 2791 -> 2763
+// us; 131K tokens, 32 heads 6622 -> 6697 us (64 rounds of the CUs: not taken).
+template <int D, int NW>
+DA_ATTN_KERNEL(D, NW) void attn_pair_kernel(Args ar, Args as, uint32_t nr, uint32_t nr8) {
+  if (blockIdx.x >= nr8)
+    attn_body<D, kSparse, NW>(as, blockIdx.x - nr8, gridDim.x - nr8);
+  else if (blockIdx.x < nr)
+    attn_body<D, kDenseRows, NW>(ar, blockIdx.x, nr);
+}
+#undef DA_ATTN_KERNEL
+
 // Step 3 of Algorithm 1 for one dense row r of one sequence and a range of
 // heads: merge the key-chunk partials of r into the dense result (log-sum-exp
 // merge), then
@@ -1400,10 +1426,9 @@ __global__ __launch_bounds__(256) void check_inputs_kernel(const int32_t* cu, in
   if (tid == 0) *result = red[0];
 }
 
+// Fills in what a launch of `nblocks` blocks derives from its tiling.
 template <int MODE>
-hipError_t launch_attn(const Args& a0, hipStream_t s, int64_t nblocks) {
-  if (nblocks <= 0) return hipSuccess;
-  Args a = a0;
+void prepare_attn(Args& a, int64_t nblocks) {
   a.fd_rtiles = make_fastdiv((uint32_t)a.n_rtiles);
   a.fd_nC = make_fastdiv((uint32_t)(a.nC > 0 ? a.nC : 1));
   a.fd_B = make_fastdiv((uint32_t)a.B);
@@ -1426,9 +1451,19 @@ hipError_t launch_attn(const Args& a0, hipStream_t s, int64_t nblocks) {
   a.xcd_log = 0;
   if (MODE == kSparse && kRowsPerWave * a.ppw * 8 >= kXcdSpread * a.n_hgroups)
     while ((2 << a.xcd_log) <= kXcdChunk && nblocks >= ((int64_t)4 * 8 * 2 << a.xcd_log)) ++a.xcd_log;
-  // dense rows a sparse workgroup stages for the fused store
-  const int pre = MODE == kSparse && a.fuse && a.gamma > 1
-                      ? a.hpw * (kRowsPerWave * a.ppw / a.gamma) * a.d * 4 : 0;
+}
+
+// Bytes of the dense rows a sparse workgroup stages for the fused store.
+int pre_bytes(const Args& a) {
+  return a.fuse && a.gamma > 1 ? a.hpw * (kRowsPerWave * a.ppw / a.gamma) * a.d * 4 : 0;
+}
+
+template <int MODE>
+hipError_t launch_attn(const Args& a0, hipStream_t s, int64_t nblocks) {
+  if (nblocks <= 0) return hipSuccess;
+  Args a = a0;
+  prepare_attn<MODE>(a, nblocks);
+  const int pre = MODE == kSparse ? pre_bytes(a) : 0;
 #define DA_ATTN(DD, W)                                                                          \
   hipLaunchKernelGGL((attn_kernel<DD, MODE, W>), dim3((unsigned)nblocks), dim3(64 * W),         \
                      (lds_bytes<DD, MODE, W>(pre)), s, a)
@@ -1477,16 +1512,12 @@ hipError_t launch_check_inputs(const int32_t* cu, int B, int max_seqlen, const i
   return hipGetLastError();
 }
 
-hipError_t launch_sparse(const Args& a, hipStream_t s) {
-  return launch_attn<kSparse>(a, s, (int64_t)a.B * a.n_hgroups * a.n_rtiles);
-}
-
 hipError_t launch_dense(const Args& a, hipStream_t s) {
   return launch_attn<kDense>(a, s, (int64_t)a.B * a.n_hgroups * a.n_rtiles);
 }
 
-hipError_t launch_dense_rows(const Args& a0, hipStream_t s) {
-  Args a = a0;
+// The strided rows' block order (see dr_n1 in Args).
+static void order_dense_rows(Args& a) {
   a.dr_n1 = a.dr_n2 = 0;
   if (!a.cu && a.nC >= 1 && a.nC <= 16 && a.gamma >= 1) {
     // Sequences of a.N tokens: the key tiles row tile rt takes from chunk c,
@@ -1518,7 +1549,43 @@ hipError_t launch_dense_rows(const Args& a0, hipStream_t s) {
       a.dr_n2 += t - z;
     }
   }
-  return launch_attn<kDenseRows>(a, s, (int64_t)a.B * a.n_hgroups * a.nC * a.n_rtiles);
+}
+
+static int64_t dense_row_blocks(const Args& a) {
+  return (int64_t)a.B * a.n_hgroups * a.nC * a.n_rtiles;
+}
+
+hipError_t launch_dense_rows(const Args& a0, hipStream_t s) {
+  Args a = a0;
+  order_dense_rows(a);
+  return launch_attn<kDenseRows>(a, s, dense_row_blocks(a));
+}
+
+hipError_t launch_sparse(const Args& a0, hipStream_t s) {
+  const int64_t ns = (int64_t)a0.B * a0.n_hgroups * a0.n_rtiles;
+  if (!a0.rows) return launch_attn<kSparse>(a0, s, ns);
+  // together with the strided rows: as many wavefronts per workgroup
+  Args ar = *a0.rows, as = a0;
+  const int64_t nr = dense_row_blocks(ar), nr8 = (nr + 7) / 8 * 8;
+  const int waves = as.hpw * as.ppw;
+  if (nr <= 0 || ns <= 0 || ar.hpw * ar.ppw != waves || nr8 + ns > INT32_MAX) return hipErrorInvalidValue;
+  order_dense_rows(ar);
+  prepare_attn<kDenseRows>(ar, nr);
+  prepare_attn<kSparse>(as, ns);
+  const dim3 g((unsigned)(nr8 + ns));
+  const int pre = pre_bytes(as);
+#define DA_PAIR(DD, W)                                                                          \
+  hipLaunchKernelGGL((attn_pair_kernel<DD, W>), g, dim3(64 * W), (lds_bytes<DD, kSparse, W>(pre)), \
+                     s, ar, as, (uint32_t)nr, (uint32_t)nr8)
+  if (as.d == 128) {
+    if (waves == 8) DA_PAIR(128, 8);
+    else DA_PAIR(128, 4);
+  } else {
+    if (waves == 8) DA_PAIR(64, 8);
+    else DA_PAIR(64, 4);
+  }
+#undef DA_PAIR
+  return hipGetLastError();
 }
 
 // Query heads per workgroup of the in-place passes over `out`: a.head_chunk, or
