@@ -278,8 +278,11 @@ da_status delta_attn_prefill_noalloc(const void* q, const void* k, const void* v
                                      void* stream);
 
 /*
- * Workspace bytes delta_attn_prefill[_varlen] needs for these sizes
+ * Workspace bytes delta_attn_prefill[_varlen] uses for these sizes
  * (max_seqlen = N for the fixed-length call).  0 if the sizes are invalid.
+ * Short sequences can use more than longer ones, as they split their key axis
+ * finer; given less, down to what key chunks of at least 2560 keys need, a
+ * call splits it coarser.
  */
 size_t da_workspace_bytes(int B, int max_seqlen, int Hq, int Hkv, int d, int gamma);
 

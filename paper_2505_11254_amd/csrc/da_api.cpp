@@ -103,8 +103,10 @@ static int64_t strided_tiles(int64_t B, int64_t N, int Hq, int G, int64_t gamma,
 // workgroup.
 // nC drops only when the partial results would pass 8 GiB, or, with a nonzero
 // `limit`, until the whole workspace fits `limit` bytes (false when even one
-// chunk does not).
-bool make_plan(int B, int max_seqlen, int Hq, int Hkv, int d, int gamma, Plan* p, size_t limit) {
+// chunk does not).  long_chunks: chunks of at least kLongChunk tiles whatever
+// the launch fills (the least workspace a call takes).
+bool make_plan(int B, int max_seqlen, int Hq, int Hkv, int d, int gamma, Plan* p, size_t limit,
+               bool long_chunks) {
   if (B < 1 || max_seqlen < 1 || Hq < 1 || Hkv < 1 || gamma < 1 || (d != 64 && d != 128))
     return false;
   if (Hq % Hkv != 0) return false;
@@ -118,7 +120,8 @@ bool make_plan(int B, int max_seqlen, int Hq, int Hkv, int d, int gamma, Plan* p
   const int hpw = heads_per_block(Hq / Hkv);
   const bool one_block = (int64_t)B * (Hq / hpw) == 1 && nR_max <= kRowsPerWave * (kAttnWaves / hpw);
   const int64_t one = one_block ? 1024 : 448;  // keys
-  const int64_t min_keys = max_seqlen <= one ? one : kKeyTile * min_tiles;
+  const int64_t min_keys = long_chunks ? kKeyTile * kLongChunk
+                           : max_seqlen <= one ? one : kKeyTile * min_tiles;
   int64_t nC = (max_seqlen + min_keys - 1) / min_keys;
   if (nC > 16) nC = 16;
   if (nC < 1) nC = 1;
@@ -384,7 +387,17 @@ da_status run_delta(const Problem& P, void* workspace, size_t workspace_bytes, v
       return DA_ERR_WORKSPACE;
   } else {
     const size_t extra = correction_floats(P.B, P.N, P.Hq, P.d, P.gamma, corr_mode) * 4;
-    if (!workspace || workspace_bytes < plan.bytes + extra) return DA_ERR_WORKSPACE;
+    if (!workspace) return DA_ERR_WORKSPACE;
+    if (workspace_bytes < plan.bytes + extra) {
+      // Short sequences may want more chunks, and a larger workspace, than longer
+      // ones.  A workspace that holds the plan with long chunks only (one laid out
+      // for the longest sequence of a serving loop, say) takes as many as fit it.
+      Plan least;
+      if (!make_plan(P.B, P.N, P.Hq, P.Hkv, P.d, P.gamma, &least, 0, true) ||
+          workspace_bytes < least.bytes + extra ||
+          !make_plan(P.B, P.N, P.Hq, P.Hkv, P.d, P.gamma, &plan, workspace_bytes - extra))
+        return DA_ERR_WORKSPACE;
+    }
     if (!aligned16(workspace)) return DA_ERR_ALIGN;
   }
   {

@@ -128,7 +128,7 @@ struct Plan {
 };
 
 bool make_plan(int B, int max_seqlen, int Hq, int Hkv, int d, int gamma, Plan* p,
-               size_t limit = 0);
+               size_t limit = 0, bool long_chunks = false);
 
 // The allocation-free entry point's workspace: a static device array of
 // kScratchBytes (da_kernels.hip).  scratch_address gives its address on

@@ -148,3 +148,27 @@ def test_block_order_covers_every_head_and_row(Hkv, G):
         torch.cuda.synchronize()
         for name, x, y in zip(("sparse", "dense", "delta"), whole, one):
             assert torch.equal(x[:, h * G:(h + 1) * G], y), (name, h)
+
+
+@pytest.mark.parametrize("N,Hq,Hkv,d,gamma", [(4021, 8, 2, 128, 64), (3000, 4, 4, 64, 48), (900, 16, 4, 128, 32)])
+def test_a_smaller_workspace_splits_the_keys_coarser(N, Hq, Hkv, d, gamma):
+    """Less than da_workspace_bytes, down to what chunks of at least 2560 keys
+    need, is taken (within rounding of the full split); less than that is refused."""
+    q, k, v, _ = make((N,), Hq, Hkv, d, seed=N)
+    up = lambda x: (x + 255) // 256 * 256
+    rows = Hq * (N // gamma + min(gamma - 1, N))
+    n = -(-N // 2560)
+    n = -(-N // (-(-(-(-N // n)) // 64) * 64))
+    least = up(rows * d * 4) + up(rows * n * d * 4) + up(rows * n * 2 * 4)
+    full = B().workspace_bytes(1, N, Hq, Hkv, d, gamma)
+    assert full > least
+    qd, kd, vd = (x.to(DEV) for x in (q, k, v))
+    kw = dict(window=64, n_sink=4, gamma=gamma)
+    ref = oracle.delta_attention(*(to_oracle_bits(x) for x in (q, k, v)), None, **kw)
+    for size in (least, (least + full) // 2 // 16 * 16, full):
+        ws = torch.empty(size, dtype=torch.uint8, device=DEV)
+        out = B().delta_attn_prefill(qd, kd, vd, workspace=ws, **kw)
+        torch.cuda.synchronize()
+        assert_parity(out, ref, f"workspace of {size}")
+    with pytest.raises(RuntimeError, match="DA_ERR_WORKSPACE"):
+        B().delta_attn_prefill(qd, kd, vd, workspace=ws[:least - 256].clone(), **kw)
