@@ -113,12 +113,12 @@ def _call(name, *args):
 
 
 def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else None
+    return t.data_ptr() if t is not None else None
 
 
 def _stream(device, stream):
     s = stream if stream is not None else torch.cuda.current_stream(device)
-    return ctypes.c_void_p(s.cuda_stream)
+    return s.cuda_stream
 
 
 def _on_device(name, t, dev, dtype):
@@ -152,6 +152,16 @@ def _check(q, k, v, out=None, cu_seqlens=None, workspace=None, block_ptr=None,
                          f"{tuple(v.shape)})")
     if k.shape[0] != q.shape[0] or k.shape[2] != q.shape[2]:
         raise ValueError("k and v must be [T, Hkv, d] with the T and d of q")
+    if cu_seqlens is not None:
+        _on_device("cu_seqlens", cu_seqlens, dev, torch.int32)
+        if cu_seqlens.dim() != 1 or cu_seqlens.numel() < 2:
+            raise ValueError("cu_seqlens must be 1-D with B + 1 >= 2 entries")
+    _check_rest(q, k, v, out, workspace, block_ptr, block_idx)
+
+
+def _check_rest(q, k, v, out=None, workspace=None, block_ptr=None, block_idx=None):
+    """The part of _check beyond the tensors that _shapes has checked."""
+    dev = q.device
     if out is not None:
         _on_device("out", out, dev, torch.bfloat16)
         if tuple(out.shape) != tuple(q.shape):
@@ -161,10 +171,6 @@ def _check(q, k, v, out=None, cu_seqlens=None, workspace=None, block_ptr=None,
             t0, t1 = _span(t)
             if o0 < t1 and t0 < o1:
                 raise ValueError(f"out must not overlap {name}")
-    if cu_seqlens is not None:
-        _on_device("cu_seqlens", cu_seqlens, dev, torch.int32)
-        if cu_seqlens.dim() != 1 or cu_seqlens.numel() < 2:
-            raise ValueError("cu_seqlens must be 1-D with B + 1 >= 2 entries")
     if workspace is not None:
         _on_device("workspace", workspace, dev, None)
     for name, t in (("block_ptr", block_ptr), ("block_idx", block_idx)):
@@ -211,10 +217,10 @@ def delta_attn_prefill(q, k, v, *, window, n_sink, gamma, B=None, cu_seqlens=Non
     B_, N, Hq, Hkv, d = _shapes(q, k, v, B, cu_seqlens, max_seqlen)
     if out is None:
         out = torch.empty_like(q)
-    nbytes = workspace_bytes(B_, N, Hq, Hkv, d, gamma)
     if workspace is None:
+        nbytes = workspace_bytes(B_, N, Hq, Hkv, d, gamma)
         workspace = torch.empty(max(nbytes, 1), dtype=torch.uint8, device=q.device)
-    _check(q, k, v, out, cu_seqlens, workspace)
+    _check_rest(q, k, v, out, workspace)
     wsz = workspace.numel() * workspace.element_size()
     st = _stream(q.device, stream)
     if cu_seqlens is None:
@@ -235,7 +241,7 @@ def delta_attn_prefill_noalloc(q, k, v, *, window, n_sink, gamma, B=None, cu_seq
     B_, N, Hq, Hkv, d = _shapes(q, k, v, B, cu_seqlens, max_seqlen)
     if out is None:
         out = torch.empty_like(q)
-    _check(q, k, v, out, cu_seqlens)
+    _check_rest(q, k, v, out)
     _call("delta_attn_prefill_noalloc", _ptr(q), _ptr(k), _ptr(v), _ptr(out), _ptr(cu_seqlens),
           B_, N, Hq, Hkv, d, window, n_sink, gamma, _stream(q.device, stream))
     return out
@@ -252,10 +258,10 @@ def delta_attn_prefill_correction(q, k, v, *, window, n_sink, gamma, mode,
     B_, N, Hq, Hkv, d = _shapes(q, k, v, B, cu_seqlens, max_seqlen)
     if out is None:
         out = torch.empty_like(q)
-    nbytes = int(load_library().da_workspace_bytes_correction(B_, N, Hq, Hkv, d, gamma, mode))
     if workspace is None:
+        nbytes = int(load_library().da_workspace_bytes_correction(B_, N, Hq, Hkv, d, gamma, mode))
         workspace = torch.empty(max(nbytes, 1), dtype=torch.uint8, device=q.device)
-    _check(q, k, v, out, cu_seqlens, workspace)
+    _check_rest(q, k, v, out, workspace)
     wsz = workspace.numel() * workspace.element_size()
     p = list(params) + [0.0] * (3 - len(params))
     _call("delta_attn_prefill_correction", _ptr(q), _ptr(k), _ptr(v), _ptr(out),
@@ -268,7 +274,7 @@ def delta_attn_prefill_steps(q, k, v, out, workspace, steps, *, window, n_sink, 
                              cu_seqlens=None, max_seqlen=None, stream=None):
     """Run the given steps of Algorithm 1 (bit mask of STEP_*) on existing buffers."""
     B_, N, Hq, Hkv, d = _shapes(q, k, v, B, cu_seqlens, max_seqlen)
-    _check(q, k, v, out, cu_seqlens, workspace)
+    _check_rest(q, k, v, out, workspace)
     wsz = workspace.numel() * workspace.element_size()
     _call("delta_attn_prefill_steps", _ptr(q), _ptr(k), _ptr(v), _ptr(out), _ptr(cu_seqlens),
           B_, N, Hq, Hkv, d, window, n_sink, gamma, _ptr(workspace), wsz,
@@ -282,7 +288,7 @@ def sparse_attn_prefill(q, k, v, *, window, n_sink, B=None, cu_seqlens=None, max
     B_, N, Hq, Hkv, d = _shapes(q, k, v, B, cu_seqlens, max_seqlen)
     if out is None:
         out = torch.empty_like(q)
-    _check(q, k, v, out, cu_seqlens)
+    _check_rest(q, k, v, out)
     st = _stream(q.device, stream)
     if cu_seqlens is None:
         _call("sparse_attn_prefill", _ptr(q), _ptr(k), _ptr(v), _ptr(out), B_, Hq, Hkv, N, d,
@@ -299,7 +305,7 @@ def dense_causal_attn_prefill(q, k, v, *, B=None, cu_seqlens=None, max_seqlen=No
     B_, N, Hq, Hkv, d = _shapes(q, k, v, B, cu_seqlens, max_seqlen)
     if out is None:
         out = torch.empty_like(q)
-    _check(q, k, v, out, cu_seqlens)
+    _check_rest(q, k, v, out)
     st = _stream(q.device, stream)
     if cu_seqlens is None:
         _call("dense_causal_attn_prefill", _ptr(q), _ptr(k), _ptr(v), _ptr(out), B_, Hq, Hkv,
@@ -333,7 +339,7 @@ def blocksparse_attn_prefill(q, k, v, *, block_q, block_ptr, block_idx, B=None,
     B_, N, Hq, Hkv, d = _shapes(q, k, v, B, cu_seqlens, max_seqlen)
     if out is None:
         out = torch.empty_like(q)
-    _check(q, k, v, out, cu_seqlens, block_ptr=block_ptr, block_idx=block_idx)
+    _check_rest(q, k, v, out, block_ptr=block_ptr, block_idx=block_idx)
     _call("blocksparse_attn_prefill", _ptr(q), _ptr(k), _ptr(v), _ptr(out), _ptr(cu_seqlens),
           B_, N, Hq, Hkv, d, block_q, *_blocks(block_ptr, block_idx, B_, Hkv, N, block_q),
           _stream(q.device, stream))
@@ -347,10 +353,10 @@ def delta_attn_prefill_blocksparse(q, k, v, *, block_q, block_ptr, block_idx, ga
     B_, N, Hq, Hkv, d = _shapes(q, k, v, B, cu_seqlens, max_seqlen)
     if out is None:
         out = torch.empty_like(q)
-    nbytes = workspace_bytes(B_, N, Hq, Hkv, d, gamma)
     if workspace is None:
+        nbytes = workspace_bytes(B_, N, Hq, Hkv, d, gamma)
         workspace = torch.empty(max(nbytes, 1), dtype=torch.uint8, device=q.device)
-    _check(q, k, v, out, cu_seqlens, workspace, block_ptr, block_idx)
+    _check_rest(q, k, v, out, workspace, block_ptr, block_idx)
     wsz = workspace.numel() * workspace.element_size()
     _call("delta_attn_prefill_blocksparse", _ptr(q), _ptr(k), _ptr(v), _ptr(out),
           _ptr(cu_seqlens), B_, N, Hq, Hkv, d, block_q,

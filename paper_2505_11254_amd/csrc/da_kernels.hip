@@ -8,10 +8,10 @@
 //      (Eq. 6); rows after the last whole group are computed densely
 //      (implementation-details appendix).
 // Steps 1 and 2 and the dense causal baseline share one attention kernel
-// template (`attn_kernel`); step 3 is `delta_epilogue_kernel`.  The fused
-// schedule runs step 2 first, merges its dense rows, and lets the sparse
-// kernel store sparse + Delta directly, which saves the in-place pass over
-// the output.
+// template (`attn_body`); step 3 is `delta_epilogue_kernel`.  The fused
+// schedule runs step 2 first, merges its dense rows (`merge_rows_kernel`), and
+// lets the sparse kernel store sparse + Delta directly, which saves the
+// in-place pass over the output.
 //
 // Tile core (one wavefront = 32 query rows, 64-key tiles, bf16 MFMA):
 //   S^T[key][row] = K Q^T   with v_mfma_f32_32x32x16_bf16: A = K rows from
@@ -1004,19 +1004,6 @@ DA_ATTN_KERNEL(D, NW) void attn_pair_kernel(Args ar, Args as, uint32_t nr, uint3
 }
 #undef DA_ATTN_KERNEL
 
-// Step 3 of Algorithm 1 for one dense row r of one sequence and a range of
-// heads: merge the key-chunk partials of r into the dense result (log-sum-exp
-// merge), then
-//   anchor row a = r*gamma:  Delta = dense - sparse(a) in fp32, out[a] = dense,
-//                            out[i] += Delta for i = a+1 .. a+gamma-1;
-//   tail row:                out[row] = dense.
-// An anchor below a.cover (a < n_sink + window: all keys 0..a are in its
-// sparse set) has Delta exactly zero and the block leaves its rows untouched;
-// with key-block lists no anchor is assumed covered (cover = 0).
-// Epilogue modes: the Delta correction itself; "recompute" (Eq. 5: the dense
-// row replaces the sparse one at anchors only).
-enum Epi { kEpiDelta = 0, kEpiRecompute = 1 };
-
 // Log-sum-exp merge of the first nc key-chunk partials of one dense row:
 // values po[cc * D] (VF floats each) under (running max, normaliser) ml[cc].
 // One pass in chunk order with a running max M: chunks with no visible key
@@ -1095,6 +1082,19 @@ __global__ __launch_bounds__(kEpiThreads) void merge_rows_kernel(Args a) {
     }
   }
 }
+
+// Step 3 of Algorithm 1 for one dense row r of one sequence and a range of
+// heads: merge the key-chunk partials of r into the dense result (log-sum-exp
+// merge), then
+//   anchor row a = r*gamma:  Delta = dense - sparse(a) in fp32, out[a] = dense,
+//                            out[i] += Delta for i = a+1 .. a+gamma-1;
+//   tail row:                out[row] = dense.
+// An anchor below a.cover (a < n_sink + window: all keys 0..a are in its
+// sparse set) has Delta exactly zero and the block leaves its rows untouched;
+// with key-block lists no anchor is assumed covered (cover = 0).
+// Epilogue modes: the Delta correction itself; "recompute" (Eq. 5: the dense
+// row replaces the sparse one at anchors only).
+enum Epi { kEpiDelta = 0, kEpiRecompute = 1 };
 
 template <int D, int EPI>
 __global__ __launch_bounds__(kEpiThreads) void delta_epilogue_kernel(Args a) {
