@@ -137,6 +137,7 @@ bool make_plan(int B, int max_seqlen, int Hq, int Hkv, int d, int gamma, Plan* p
     p->nR_max = (int)nR_max;
     p->nC = (int)n;
     p->chunk = (int)chunk;
+    p->finer = n > (max_seqlen + kKeyTile * kLongChunk - 1) / (kKeyTile * kLongChunk);
     p->sa_floats = (size_t)B * Hq * nR_max * d;  // sparse anchor rows, or merged dense rows
     p->part_o_floats = (size_t)B * Hq * nR_max * n * d;
     p->part_ml_floats = (size_t)B * Hq * nR_max * n * 2;
@@ -432,6 +433,7 @@ da_status run_delta(const Problem& P, void* workspace, size_t workspace_bytes, v
   a.nR_max = plan.nR_max;
   a.nC = plan.nC;
   a.chunk = plan.chunk;
+  a.split_ref = plan.finer;
   a.corr_mode = corr_mode;
   a.corr_p[0] = p0;
   a.corr_p[1] = p1;

@@ -103,6 +103,7 @@ struct Args {
   int nR_max;         // max dense rows per sequence (anchors + tail rows)
   int nC;             // key chunks per dense row (split of the key axis)
   int chunk;          // keys per chunk, a multiple of kKeyTile
+  int split_ref;      // the plan's `finer`
   int head_chunk;     // query heads per epilogue workgroup
 
   // Correction variants of step 5 (see delta_attn_prefill_correction).
@@ -123,6 +124,7 @@ struct Args {
 // Sizes of the Delta path's workspace for a problem; all in elements/bytes.
 struct Plan {
   int nA_max, nR_max, nC, chunk;
+  int finer;  // 1: more key chunks than chunks of at least 2560 keys would make
   size_t sa_floats, part_o_floats, part_ml_floats;  // sa: nR_max rows per (sequence, head)
   size_t bytes;
 };

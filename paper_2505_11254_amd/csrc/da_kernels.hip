@@ -384,7 +384,7 @@ __device__ __forceinline__ void attn_body(const Args& a, uint32_t bid, uint32_t 
                           (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)((uintptr_t)vbase >> 32)) << 32;
   const int L_s = __builtin_amdgcn_readfirstlane(L);
   const uint32_t smem_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint16_t*)smem;
-  auto dma = [&](int tile, int stage) {
+  auto dma = [&](int tile, int stage, bool values = true) {
     if (tile < 0) return;  // a list entry the key set ignores
     const uint32_t tu = (uint32_t)__builtin_amdgcn_readfirstlane(tile);
     const uint64_t off = (uint64_t)tu * tile_bytes;
@@ -401,7 +401,7 @@ __device__ __forceinline__ void attn_body(const Args& a, uint32_t bid, uint32_t 
     for (int i = 0; i < RPW; ++i) {
       const uint32_t region = (uint32_t)((wave_s * RPW + i) * 512) * 2;  // bytes
       dma16(kr, st0 + region, dma_koff[i]);
-      dma16(vr, st0 + (uint32_t)LD::kElems * 2 + region, dma_voff[i]);
+      if (values) dma16(vr, st0 + (uint32_t)LD::kElems * 2 + region, dma_voff[i]);
     }
   };
 
@@ -463,6 +463,18 @@ __device__ __forceinline__ void attn_body(const Args& a, uint32_t bid, uint32_t 
   bool has_ref = false;
   f32x16 nref = f32x16{};
   float l = 0.f;        // this lane's share of the softmax normaliser
+  // Key axis split finer than into long chunks (a.split_ref): the references of
+  // chunks past the first differ from `ref0`, the one that the row takes from the
+  // sequence's first tile, by whole powers of two.  Then every weight of the row
+  // rounds to bf16 as it does in one chunk, and as the anchor's sparse row rounds
+  // it, whose first tile is the same where the sinks cover it: the roundings of the
+  // keys that both rows have cancel in Delta however finely the keys are split
+  // (corrected rows against 64 bits, 2500 tokens, window 1024, 16 chunks: relative
+  // error 0.00246, as in one chunk, in place of 0.00296; 4021 tokens, window 2048
+  // 0.00245, 0.00274 in two long chunks).  It costs the keys of one more tile per
+  // workgroup, 0-1 % of a whole call.
+  const bool split = MODE == kDenseRows && a.split_ref && c > 0;
+  float ref0 = 0.f;
   typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
   const bf16x2 ones2 = {(__bf16)1.0f, (__bf16)1.0f};
 
@@ -520,6 +532,24 @@ __device__ __forceinline__ void attn_body(const Args& a, uint32_t bid, uint32_t 
     }
   };
 
+  // The row's largest score of a tile in base-2 units (before the reference is
+  // added back): over the 32 scores of this lane (a tree of 3-input max), then
+  // across the lane pair l, l^32 that shares the row.
+  auto row_max = [&](const f32x16& s0, const f32x16& s1) -> float {
+    float t3[11];
+#pragma unroll
+    for (int i = 0; i < 5; ++i) t3[i] = fmaxf(s0[3 * i], fmaxf(s0[3 * i + 1], s0[3 * i + 2]));
+#pragma unroll
+    for (int i = 0; i < 5; ++i) t3[5 + i] = fmaxf(s1[3 * i], fmaxf(s1[3 * i + 1], s1[3 * i + 2]));
+    t3[10] = fmaxf(s0[15], s1[15]);
+    float mx = fmaxf(fmaxf(fmaxf(t3[0], t3[1]), fmaxf(t3[2], t3[3])),
+                     fmaxf(fmaxf(t3[4], t3[5]), fmaxf(t3[6], t3[7])));
+    mx = fmaxf(mx, fmaxf(t3[8], fmaxf(t3[9], t3[10])));
+    const auto pr = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx),
+                                                     false, false);
+    return qscale * fmaxf(__uint_as_float(pr[0]), __uint_as_float(pr[1]));
+  };
+
   // Online-softmax update with one tile's scores: the accumulators hold
   // s = q.k - ref / c, so c s = logit - ref in base-2 units, with c =
   // log2(e)/sqrt(d) applied in fp32 here (the queries stay as given); adds
@@ -573,28 +603,15 @@ __device__ __forceinline__ void attn_body(const Args& a, uint32_t bid, uint32_t 
     float t = INFINITY;
     if (!__any(!has_ref)) t = weights();
     if (__any(!(t <= 8192.f))) {
-      // row max over the 32 scores of this lane (a tree of 3-input max), then
-      // across the lane pair l, l^32 that shares the row
-      float t3[11];
-#pragma unroll
-      for (int i = 0; i < 5; ++i) t3[i] = fmaxf(s0[3 * i], fmaxf(s0[3 * i + 1], s0[3 * i + 2]));
-#pragma unroll
-      for (int i = 0; i < 5; ++i) t3[5 + i] = fmaxf(s1[3 * i], fmaxf(s1[3 * i + 1], s1[3 * i + 2]));
-      t3[10] = fmaxf(s0[15], s1[15]);
-      float mx = fmaxf(fmaxf(fmaxf(t3[0], t3[1]), fmaxf(t3[2], t3[3])),
-                       fmaxf(fmaxf(t3[4], t3[5]), fmaxf(t3[6], t3[7])));
-      mx = fmaxf(mx, fmaxf(t3[8], fmaxf(t3[9], t3[10])));
-      {
-        const auto pr = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx),
-                                                         false, false);
-        mx = qscale * fmaxf(__uint_as_float(pr[0]), __uint_as_float(pr[1]));  // base 2
-      }
+      const float mx = row_max(s0, s1);
       // a lane without a reference takes its tile max (if it sees any key);
       // one with a reference moves only up
       const bool seen = mx != -INFINITY;
       const bool grow = has_ref ? mx > 8.f : seen;
       if (__any(grow)) {
-        const float dm = has_ref ? fmaxf(mx, 0.f) : (seen ? mx : 0.f);
+        float up = mx;
+        if (split) up = has_ref ? ceilf(mx) : ref0 + ceilf(mx - ref0);
+        const float dm = has_ref ? fmaxf(up, 0.f) : (seen ? up : 0.f);
         const float alpha = has_ref ? fast_exp2(-dm) : 0.f;  // l and O are still zero without one
         ref += dm;
         has_ref = has_ref || seen;
@@ -659,6 +676,7 @@ __device__ __forceinline__ void attn_body(const Args& a, uint32_t bid, uint32_t 
 #pragma unroll
   for (int p = 0; p < NS - 1; ++p)
     if (p < n_iter) dma(tile_at(p), p);
+  if (split) dma(0, NS - 1, false);  // (its keys, into the stage that fills last)
 
   // Fused store: the merged dense rows of the block's anchors whose Delta is
   // not zero (anchor slot = head in block * groups per slab + group in slab),
@@ -731,6 +749,14 @@ __device__ __forceinline__ void attn_body(const Args& a, uint32_t bid, uint32_t 
       qf[kk] = *(const bf16x8*)(qst + col * D + (((2 * kk + half) ^ (col & (QCPR - 1))) * 8));
     // the fragments are in registers before the barrier after which stage 1 fills
     __builtin_amdgcn_s_waitcnt(0xC07F);
+  }
+  if (split) {
+    // (every row that sees this chunk sees all of tile 0)
+    __syncthreads();
+    f32x16 s0, s1;
+    qk(smem + (NS - 1) * LD::stageElems, 0, 0, s0, s1);
+    const float m0 = row_max(s0, s1);
+    ref0 = fabsf(m0) < 1e30f ? m0 : 0.f;
   }
   if (dsrc) *(f32x4*)(dpre + tid * 4) = dreg;
   for (int u = tid + kThreads; u < nvec; u += kThreads)
