@@ -1214,13 +1214,18 @@ __global__ __launch_bounds__(kEpiThreads) void delta_epilogue_kernel(Args a) {
 // channels of one head (64-byte accesses), which gives B * Hq * d / kScanCh
 // workgroups of 16 wavefronts; with one thread per channel the scan was one
 // serial chain on 16 CUs (64K tokens, 32 heads, gamma 64: 73 -> 15 us for
-// the EMA).
+// the EMA).  A diverging filter's A^(segment) may pass the range of floats, and a
+// state may stop being finite; times the exact zeros of covered anchors, or of A,
+// that would make NaN of rows whose correction is finite.  Such channels take their
+// steps in order, one thread each.
 constexpr int kScanCh = 16, kScanSegs = 64;
+constexpr double kScanMaxPower = 1e30;  // largest entry of A^(segment) that segments take
 template <int CORR>
 __global__ __launch_bounds__(kScanCh * kScanSegs) void corr_scan_kernel(Args a) {
   constexpr int S = CORR == 3 ? 1 : 3;  // state size
   __shared__ float st[kScanSegs][S][kScanCh];
   __shared__ float Ap[S * S];
+  __shared__ int in_order;  // 1: no segments
   const int cl = threadIdx.x % kScanCh, seg = threadIdx.x / kScanCh;
   const int64_t ch0 = (int64_t)blockIdx.x * kScanCh;
   const int64_t per_seq = (int64_t)a.Hq * a.d;
@@ -1268,9 +1273,9 @@ __global__ __launch_bounds__(kScanCh * kScanSegs) void corr_scan_kernel(Args a) 
 #pragma unroll
     for (int i = 0; i < S; ++i) x[i] = y[i];
   };
-  // runs the segment from state x: batches of kB loads go out together
+  // runs the anchors [i0, i1) from state x: batches of kB loads go out together
   constexpr int kB = 16;
-  auto run = [&](float* x, bool store) {
+  auto run = [&](float* x, int i0, int i1, bool store) {
     for (int i = i0; i < i1; i += kB) {
       float buf[kB];
 #pragma unroll
@@ -1287,13 +1292,14 @@ __global__ __launch_bounds__(kScanCh * kScanSegs) void corr_scan_kernel(Args a) 
 
   if (threadIdx.x == kScanCh * kScanSegs - 1) {
     // A^len by repeated squaring, in 64 bits (a marginally stable filter's
-    // powers cancel)
+    // powers cancel); entries stay finite, as products end past kScanMaxPower
     double P[S][S], Q[S][S];
     for (int i = 0; i < S; ++i)
       for (int j = 0; j < S; ++j) {
         P[i][j] = i == j ? 1.0 : 0.0;
         Q[i][j] = A[i][j];
       }
+    bool fits = true;
     auto mul = [&](double (*X)[S], double (*Y)[S]) {  // X = X Y
       double Z[S][S];
       for (int i = 0; i < S; ++i)
@@ -1302,23 +1308,30 @@ __global__ __launch_bounds__(kScanCh * kScanSegs) void corr_scan_kernel(Args a) 
           for (int k = 0; k < S; ++k) Z[i][j] += X[i][k] * Y[k][j];
         }
       for (int i = 0; i < S; ++i)
-        for (int j = 0; j < S; ++j) X[i][j] = Z[i][j];
+        for (int j = 0; j < S; ++j) {
+          X[i][j] = Z[i][j];
+          fits = fits && fabs(Z[i][j]) <= kScanMaxPower;
+        }
     };
-    for (int n = len; n > 0; n >>= 1) {
+    for (int i = 0; i < S; ++i)
+      for (int j = 0; j < S; ++j) fits = fits && fabs(Q[i][j]) <= kScanMaxPower;
+    for (int n = len; n > 0 && fits; n >>= 1) {
       if (n & 1) mul(P, Q);
-      mul(Q, Q);
+      if (n > 1 && fits) mul(Q, Q);
     }
     for (int i = 0; i < S; ++i)
-      for (int j = 0; j < S; ++j) Ap[i * S + j] = (float)P[i][j];
+      for (int j = 0; j < S; ++j) Ap[i * S + j] = fits ? (float)P[i][j] : 0.f;
+    in_order = !fits;
   }
   float x[S] = {};
-  run(x, false);
+  run(x, i0, i1, false);
 #pragma unroll
   for (int i = 0; i < S; ++i) st[seg][i][cl] = x[i];
   __syncthreads();
-  if (seg == 0) {
+  if (seg == 0 && !in_order) {
     float e[S] = {};
     e[0] = dl[0];
+    bool finite = true;
     for (int sg = 0; sg < kScanSegs; ++sg) {
       float y[S];
 #pragma unroll
@@ -1329,13 +1342,24 @@ __global__ __launch_bounds__(kScanCh * kScanSegs) void corr_scan_kernel(Args a) 
         for (int j = S - 1; j >= 0; --j) y[i] = __builtin_fmaf(Ap[i * S + j], e[j], y[i]);
       }
 #pragma unroll
-      for (int i = 0; i < S; ++i) e[i] = y[i];
+      for (int i = 0; i < S; ++i) {
+        finite = finite && (__float_as_uint(y[i]) & 0x7f800000u) != 0x7f800000u;
+        e[i] = y[i];
+      }
     }
+    if (!finite) in_order = 1;
   }
   __syncthreads();
+  if (in_order) {  // uniform over the block
+    if (seg != 0) return;
+    x[0] = dl[0];
+    for (int i = 1; i < S; ++i) x[i] = 0.f;
+    run(x, first, nA, true);
+    return;
+  }
 #pragma unroll
   for (int i = 0; i < S; ++i) x[i] = st[seg][i][cl];
-  run(x, true);
+  run(x, i0, i1, true);
 }
 
 // Adds the per-row correction of a smoothing variant to the gamma rows of one

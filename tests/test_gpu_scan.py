@@ -1,0 +1,40 @@
+"""The recurrences of the smoothing corrections where they leave the usual range."""
+from __future__ import annotations
+
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda"
+
+
+def B():
+    from paper_2505_11254_amd import binding
+    return binding
+
+
+def make(lens, Hq, Hkv, d, seed):
+    from paper_2505_11254_amd.inputs import random_qkv
+    return [x.to(DEV) for x in random_qkv(lens, Hq, Hkv, d, seed, device="cpu")]
+
+
+# gains whose closed loop grows by 1.362 (20000 anchors: 1e42 over a 64th of them),
+# 19 and 2e5 per anchor
+@pytest.mark.parametrize("N,d,params,window", [
+    (20000, 64, (0.1, 1.0, 1.0), 2048), (20000, 64, (0.1, 1.0, 1.0), 20000),
+    (2100, 128, (20.0, 0.0, 0.0), 900), (2100, 64, (20.0, 0.0, 0.0), 4096),
+    (300, 64, (2e5, 1.0, 1.0), 200)])
+def test_a_diverging_filter_keeps_the_rows_before_its_first_delta(N, d, params, window):
+    """Anchors whose key set is whole have a Delta of exactly zero, and so has the
+    filter until the first other anchor: their rows stay the sparse rows bit for bit,
+    and the rows that follow are finite until the filter itself is not."""
+    n_sink = 1
+    q, k, v, _ = make((N,), 1, 1, d, seed=N + d)
+    out = B().delta_attn_prefill_correction(q, k, v, window=window, n_sink=n_sink, gamma=1,
+                                            mode=B().CORR_ABG, params=params)
+    sparse = B().sparse_attn_prefill(q, k, v, window=window, n_sink=n_sink)
+    torch.cuda.synchronize()
+    cover = min(N, window + n_sink)
+    assert torch.equal(out[:cover], sparse[:cover])
+    assert torch.isfinite(out[:cover + 6].float()).all()
