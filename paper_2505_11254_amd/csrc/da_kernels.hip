@@ -1221,13 +1221,13 @@ __global__ __launch_bounds__(kEpiThreads) void delta_epilogue_kernel(Args a) {
 constexpr int kScanCh = 16, kScanSegs = 64;
 constexpr double kScanMaxPower = 1e30;  // largest entry of A^(segment) that segments take
 template <int CORR>
-__global__ __launch_bounds__(kScanCh * kScanSegs) void corr_scan_kernel(Args a) {
+__global__ __launch_bounds__(kScanCh * kScanSegs) void corr_scan_kernel(Args a, int64_t block0) {
   constexpr int S = CORR == 3 ? 1 : 3;  // state size
   __shared__ float st[kScanSegs][S][kScanCh];
   __shared__ float Ap[S * S];
   __shared__ int in_order;  // 1: no segments
   const int cl = threadIdx.x % kScanCh, seg = threadIdx.x / kScanCh;
-  const int64_t ch0 = (int64_t)blockIdx.x * kScanCh;
+  const int64_t ch0 = (block0 + blockIdx.x) * kScanCh;
   const int64_t per_seq = (int64_t)a.Hq * a.d;
   const int b = (int)(ch0 / per_seq);
   const int h = (int)((ch0 % per_seq) / a.d);
@@ -1699,13 +1699,20 @@ hipError_t launch_correction(const Args& a0, hipStream_t s) {
   Args a = a0;
   if (a.corr_mode < 2) return hipSuccess;
   if (a.corr_mode >= 3) {
-    const dim3 g((unsigned)((int64_t)a.B * a.Hq * a.d / kScanCh)), t(kScanCh * kScanSegs);
-    if (a.corr_mode == 3)
-      hipLaunchKernelGGL(corr_scan_kernel<3>, g, t, 0, s, a);
-    else
-      hipLaunchKernelGGL(corr_scan_kernel<4>, g, t, 0, s, a);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    // (a dispatch holds fewer than 2^32 threads: 65536 (sequence, head) pairs of 64
+    // channels go in one launch of 2^28)
+    constexpr int64_t kMaxBlocks = 1 << 18;
+    const int64_t blocks = (int64_t)a.B * a.Hq * a.d / kScanCh;
+    const dim3 t(kScanCh * kScanSegs);
+    for (int64_t b0 = 0; b0 < blocks; b0 += kMaxBlocks) {
+      const dim3 g((unsigned)std::min(kMaxBlocks, blocks - b0));
+      if (a.corr_mode == 3)
+        hipLaunchKernelGGL(corr_scan_kernel<3>, g, t, 0, s, a, b0);
+      else
+        hipLaunchKernelGGL(corr_scan_kernel<4>, g, t, 0, s, a, b0);
+      const hipError_t e = hipGetLastError();
+      if (e != hipSuccess) return e;
+    }
   }
   a.head_chunk = epilogue_heads(a, a.nA_max);
   const unsigned lds = (unsigned)(2 * a.head_chunk * a.d * 4);

@@ -38,3 +38,21 @@ def test_a_diverging_filter_keeps_the_rows_before_its_first_delta(N, d, params, 
     cover = min(N, window + n_sink)
     assert torch.equal(out[:cover], sparse[:cover])
     assert torch.isfinite(out[:cover + 6].float()).all()
+
+
+@pytest.mark.parametrize("mode,params", [(3, (0.3, 0.0, 0.0)), (4, (0.2, 5e-2, 3.5e-3))])
+def test_more_channels_than_one_launch_takes(mode, params):
+    """32768 sequences of 32 heads: 2^32 threads of the scan, more than one dispatch
+    holds.  Any part of the batch gives the same bits by itself."""
+    nb, L, Hq, d = 32768, 4, 32, 64
+    g = torch.Generator(device=DEV)
+    g.manual_seed(mode)
+    rand = lambda H: torch.randn((nb * L, H, d), generator=g, device=DEV, dtype=torch.bfloat16)
+    q, k, v = rand(Hq), rand(1), rand(1)
+    kw = dict(window=1, n_sink=0, gamma=2, mode=mode, params=params)
+    out = B().delta_attn_prefill_correction(q, k, v, B=nb, **kw)
+    for b0 in (0, 8191, 16383, nb - 16):
+        part = slice(b0 * L, (b0 + 16) * L)
+        some = B().delta_attn_prefill_correction(*(x[part].contiguous() for x in (q, k, v)), B=16, **kw)
+        torch.cuda.synchronize()
+        assert torch.equal(out[part], some), b0
