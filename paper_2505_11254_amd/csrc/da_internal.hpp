@@ -97,8 +97,8 @@ struct Args {
   float* dense;       // [B][Hq][nR_max][d]      merged dense rows, fp32 (fused schedule;
                       //                          the same memory as sa)
   float* part_o;      // [B][Hq][nR_max][nC][d]  unnormalised partial outputs of dense rows
-  float* part_ml;     // [B][Hq][nR_max][nC][2]  (running max * scale_log2, normaliser);
-                      // nullptr: one chunk, part_o takes normalised rows
+  float* part_ml;     // [B][Hq][nR_max][nC][2]  (running max * scale_log2, normaliser)
+  int merged;         // 1: one key chunk, whose strided kernel also writes `dense`
   int nA_max;         // max anchors per sequence: floor(max_seqlen / gamma)
   int nR_max;         // max dense rows per sequence (anchors + tail rows)
   int nC;             // key chunks per dense row (split of the key axis)

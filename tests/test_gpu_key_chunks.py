@@ -55,3 +55,28 @@ def test_a_finer_key_split_costs_no_precision(N, d, window, gamma):
         err.append(np.linalg.norm(out[rows] - ref[rows]) / np.linalg.norm(ref[rows]))
     print("rel error: long chunks %.6f, finer %.6f" % tuple(err))
     assert err[1] <= 1.02 * err[0]
+
+
+@pytest.mark.parametrize("N,Hq,Hkv,d", [(300, 8, 2, 128), (448, 1, 1, 64), (40, 4, 4, 64)])
+@pytest.mark.parametrize("first", ["whole", "all steps", "both steps"])
+def test_the_merge_alone_follows_any_call_that_ran_the_strided_rows(N, Hq, Hkv, d, first):
+    """One key chunk: the call that needs no merge leaves what a merge on its own
+    reads, and what the sparse step on its own reads."""
+    q, k, v, _ = (x.to(DEV) for x in make((N,), Hq, Hkv, d, seed=N))
+    kw = dict(window=40, n_sink=3, gamma=32)
+    b = B()
+    assert b.launch_plan(1, N, Hq, Hkv, d, 32)["key_chunks"] == 1
+    want = b.delta_attn_prefill(q, k, v, **kw)
+    ws = torch.full((b.workspace_bytes(1, N, Hq, Hkv, d, 32) // 4,), float("nan"), device=DEV)
+    out = torch.full_like(q, float("nan"))
+    step = lambda bits: b.delta_attn_prefill_steps(q, k, v, out, ws, bits | b.STEP_FUSED, **kw)
+    if first == "whole":
+        b.delta_attn_prefill(q, k, v, out=out, workspace=ws, **kw)
+    else:
+        step(b.STEP_ALL if first == "all steps" else b.STEP_DENSE_ROWS | b.STEP_CORRECT)
+    for again in (b.STEP_SPARSE, b.STEP_CORRECT, b.STEP_SPARSE):
+        out.fill_(float("nan")) if again == b.STEP_SPARSE else None
+        step(again)
+        if again == b.STEP_SPARSE:
+            torch.cuda.synchronize()
+            assert torch.equal(out, want)
