@@ -55,16 +55,16 @@ typedef enum {
   DA_ERR_PARAM = 3,       /* window < 1, n_sink < 0 or gamma < 1 */
   DA_ERR_UNSUPPORTED = 4, /* d not in {64, 128}, or the current device is not gfx950 */
   DA_ERR_ALIGN = 5,       /* a tensor or workspace pointer is not 16-byte aligned */
-  DA_ERR_WORKSPACE = 6,   /* workspace NULL or smaller than da_workspace_bytes() */
+  DA_ERR_WORKSPACE = 6,   /* workspace NULL or too small (see da_workspace_bytes()) */
   DA_ERR_HIP = 7          /* a HIP runtime call failed; see da_last_hip_error() */
 } da_status;
 
 /*
  * Delta Attention prefill (Algorithm 1), fixed-length batch of B sequences
  * of N tokens.  Writes the corrected output to `out`.
- * workspace: device memory of at least da_workspace_bytes(B, N, Hq, Hkv, d,
- * gamma) bytes, used for the strided rows' partial results and fp32 rows at
- * the anchors; its contents on entry do not matter.
+ * workspace: device memory of da_workspace_bytes(B, N, Hq, Hkv, d, gamma)
+ * bytes or more (less: see there), used for the strided rows' partial results
+ * and fp32 rows at the anchors; its contents on entry do not matter.
  * Two launch schedules compute the result (see delta_attn_prefill_steps);
  * this call takes the fused one whenever da_fused_supported(Hq, Hkv, gamma),
  * else the unfused one.  The fused schedule rounds a corrected row to bf16
@@ -107,7 +107,10 @@ da_status delta_attn_prefill_varlen(const void* q, const void* k, const void* v,
  * slab of a sparse-kernel workgroup (da_fused_supported); otherwise
  * DA_STEP_FUSED gives DA_ERR_UNSUPPORTED.  All steps of one schedule, in
  * order (or one call with DA_STEP_ALL, plus DA_STEP_FUSED for the fused
- * one), equal one delta_attn_prefill[_varlen] call that takes that schedule.
+ * one), equal one delta_attn_prefill[_varlen] call that takes that schedule,
+ * given da_workspace_bytes() or more.  DA_STEP_DENSE_ROWS and DA_STEP_CORRECT in
+ * calls of their own lay the partials out alike for any two sizes from
+ * da_workspace_bytes() on, and for any two accepted ones below it.
  * cu_seqlens may be NULL: then B sequences of max_seqlen tokens each.
  * Other arguments and errors as delta_attn_prefill_varlen; a `steps` value
  * with none of the three step bits, or with other bits, gives DA_ERR_PARAM.
@@ -282,7 +285,8 @@ da_status delta_attn_prefill_noalloc(const void* q, const void* k, const void* v
  * (max_seqlen = N for the fixed-length call).  0 if the sizes are invalid.
  * Short sequences can use more than longer ones, as they split their key axis
  * finer; given less, down to what key chunks of at least 2560 keys need, a
- * call splits it coarser.
+ * call splits it coarser (which changes the result by rounding), and one given
+ * less than that returns DA_ERR_WORKSPACE.
  */
 size_t da_workspace_bytes(int B, int max_seqlen, int Hq, int Hkv, int d, int gamma);
 

@@ -393,10 +393,16 @@ da_status run_delta(const Problem& P, void* workspace, size_t workspace_bytes, v
       // Short sequences may want more chunks, and a larger workspace, than longer
       // ones.  A workspace that holds the plan with long chunks only (one laid out
       // for the longest sequence of a serving loop, say) takes as many as fit it.
+      // Calls that pass partials from one to the other take the long chunks then,
+      // so that calls given different sizes agree on the layout.
       Plan least;
       if (!make_plan(P.B, P.N, P.Hq, P.Hkv, P.d, P.gamma, &least, 0, true) ||
-          workspace_bytes < least.bytes + extra ||
-          !make_plan(P.B, P.N, P.Hq, P.Hkv, P.d, P.gamma, &plan, workspace_bytes - extra))
+          workspace_bytes < least.bytes + extra)
+        return DA_ERR_WORKSPACE;
+      const unsigned both = DA_STEP_DENSE_ROWS | DA_STEP_CORRECT;
+      if ((steps & both) != 0u && (steps & both) != both)
+        plan = least;
+      else if (!make_plan(P.B, P.N, P.Hq, P.Hkv, P.d, P.gamma, &plan, workspace_bytes - extra))
         return DA_ERR_WORKSPACE;
     }
     if (!aligned16(workspace)) return DA_ERR_ALIGN;

@@ -80,3 +80,37 @@ def test_the_merge_alone_follows_any_call_that_ran_the_strided_rows(N, Hq, Hkv, 
         if again == b.STEP_SPARSE:
             torch.cuda.synchronize()
             assert torch.equal(out, want)
+
+
+@pytest.mark.parametrize("fused", [True, False])
+def test_steps_agree_on_the_layout_whatever_smaller_workspace_each_is_given(fused):
+    """Strided rows and merge in calls of their own, on one buffer, told of different
+    sizes below the full one: one layout, that of the long chunks."""
+    N, Hq, Hkv, d, gamma = 6000, 4, 2, 128, 64
+    b = B()
+    q, k, v, _ = (x.to(DEV) for x in make((N,), Hq, Hkv, d, seed=N))
+    kw = dict(window=100, n_sink=3, gamma=gamma)
+    full, least = b.workspace_bytes(1, N, Hq, Hkv, d, gamma), long_chunk_bytes(N, Hq, d, gamma)
+    middle = (least + full) // 512 * 256
+    ws = torch.empty(full, dtype=torch.uint8, device=DEV)
+    F = b.STEP_FUSED if fused else 0
+
+    def run(out, size, bits):
+        b.delta_attn_prefill_steps(q, k, v, out, ws[:size], bits | F, **kw)
+        torch.cuda.synchronize()
+
+    want = torch.empty_like(q)
+    run(want, least, b.STEP_ALL)
+    order = [b.STEP_DENSE_ROWS, b.STEP_CORRECT, b.STEP_SPARSE] if fused else \
+            [b.STEP_SPARSE, b.STEP_DENSE_ROWS, b.STEP_CORRECT]
+    for sizes in ((least, middle, full - 256), (full - 256, least, middle), (middle, full - 256, least)):
+        ws.fill_(255)
+        out = torch.empty_like(q)
+        for bits, size in zip(order, sizes):
+            run(out, size, bits)
+        assert torch.equal(out, want), sizes
+    whole = torch.empty_like(q)
+    run(whole, full, b.STEP_ALL)
+    for bits in order:
+        run(out, full, bits)
+    assert torch.equal(out, whole)
