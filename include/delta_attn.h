@@ -284,9 +284,12 @@ da_status delta_attn_prefill_noalloc(const void* q, const void* k, const void* v
  * Workspace bytes delta_attn_prefill[_varlen] uses for these sizes
  * (max_seqlen = N for the fixed-length call).  0 if the sizes are invalid.
  * Short sequences can use more than longer ones, as they split their key axis
- * finer; given less, down to what key chunks of at least 2560 keys need, a
- * call splits it coarser (which changes the result by rounding), and one given
- * less than that returns DA_ERR_WORKSPACE.
+ * finer, and very long ones less than shorter ones, as their partial results
+ * are held to 8 GiB by fewer chunks.  Given less, down to what key chunks of at
+ * least 2560 keys need, a call splits it coarser (which changes the result by
+ * rounding), and one given less than that returns DA_ERR_WORKSPACE.  A
+ * workspace laid out for a longer max_seqlen with the other sizes the same
+ * serves every whole-path call.
  */
 size_t da_workspace_bytes(int B, int max_seqlen, int Hq, int Hkv, int d, int gamma);
 

@@ -15,6 +15,7 @@ namespace da {
 namespace {
 
 constexpr int kCUs = 256;  // of a gfx950
+constexpr int64_t kPartialBudget = (int64_t)8 << 30;  // bytes of the strided rows' partials
 
 thread_local int g_last_hip_error = 0;
 
@@ -101,7 +102,7 @@ static int64_t strided_tiles(int64_t B, int64_t N, int Hq, int G, int64_t gamma,
 // which needs no merge (300 tokens 25.0 us against 26.7 us in two; 520 tokens
 // 30.8 us against 26.7 us), and so do up to 1024 keys of a problem of a single
 // workgroup.
-// nC drops only when the partial results would pass 8 GiB, or, with a nonzero
+// nC drops only when the partial results would pass kPartialBudget, or, with a nonzero
 // `limit`, until the whole workspace fits `limit` bytes (false when even one
 // chunk does not).  long_chunks: chunks of at least kLongChunk tiles whatever
 // the launch fills (the least workspace a call takes).
@@ -126,8 +127,7 @@ bool make_plan(int B, int max_seqlen, int Hq, int Hkv, int d, int gamma, Plan* p
   if (nC > 16) nC = 16;
   if (nC < 1) nC = 1;
   const int64_t per_chunk_bytes = (int64_t)B * Hq * nR_max * (d + 2) * 4;
-  const int64_t budget = (int64_t)8 << 30;
-  while (nC > 1 && per_chunk_bytes * nC > budget) --nC;
+  while (nC > 1 && per_chunk_bytes * nC > kPartialBudget) --nC;
   auto up = [](size_t x) { return (x + 255) / 256 * 256; };
   auto fill = [&](int64_t want) {
     int64_t chunk = (max_seqlen + want - 1) / want;
@@ -393,14 +393,20 @@ da_status run_delta(const Problem& P, void* workspace, size_t workspace_bytes, v
       // Short sequences may want more chunks, and a larger workspace, than longer
       // ones.  A workspace that holds the plan with long chunks only (one laid out
       // for the longest sequence of a serving loop, say) takes as many as fit it.
+      // So does one that a longer sequence's plan may fill where kPartialBudget
+      // holds that to fewer chunks, n < plan.nC of them: then n + 1 chunks of its
+      // rows pass the budget, and n with the d fp32 values per row beside them take
+      // (n + d / (d + 2)) / (n + 1) of it at the least, which is smallest at n = 1.
       // Calls that pass partials from one to the other take the long chunks then,
       // so that calls given different sizes agree on the layout.
       Plan least;
-      if (!make_plan(P.B, P.N, P.Hq, P.Hkv, P.d, P.gamma, &least, 0, true) ||
-          workspace_bytes < least.bytes + extra)
-        return DA_ERR_WORKSPACE;
+      if (!make_plan(P.B, P.N, P.Hq, P.Hkv, P.d, P.gamma, &least, 0, true)) return DA_ERR_WORKSPACE;
       const unsigned both = DA_STEP_DENSE_ROWS | DA_STEP_CORRECT;
-      if ((steps & both) != 0u && (steps & both) != both)
+      const bool passed_on = (steps & both) != 0u && (steps & both) != both;
+      const size_t longer = (size_t)(kPartialBudget / (P.d + 2) * (P.d + 1));
+      const size_t floor = passed_on || least.bytes < longer ? least.bytes : longer;
+      if (workspace_bytes < floor + extra) return DA_ERR_WORKSPACE;
+      if (passed_on)
         plan = least;
       else if (!make_plan(P.B, P.N, P.Hq, P.Hkv, P.d, P.gamma, &plan, workspace_bytes - extra))
         return DA_ERR_WORKSPACE;

@@ -274,3 +274,35 @@ def test_binding_abi_version_matches_header_and_library(monkeypatch):
     with pytest.raises(RuntimeError, match="ABI version"):
         binding.load_library()
     monkeypatch.setattr(binding, "_lib", None)
+
+
+@pytest.mark.parametrize("N,longer,gamma,d", [(258000, 262144, 8, 128), (500000, 520000, 8, 128),
+                                              (250000, 262144, 4, 64), (90000, 1 << 20, 2, 128)])
+def test_a_longer_sequences_workspace_serves_shorter_ones(lib, N, longer, gamma, d):
+    """Past the lengths where fewer chunks hold the partials to their budget a longer
+    sequence's workspace is the smaller one.  (The size is looked at before the
+    alignment, so a misaligned workspace tells an accepted size, 5, from a refused one,
+    6, without a launch.)"""
+    ws = lib.da_workspace_bytes
+    size = ws(1, longer, 32, 8, d, gamma)
+    call = lambda size: delta(lib, N=N, Hq=32, Hkv=8, d=d, gamma=gamma, ws=FAKE + 8, wsz=size)
+    assert call(size) == 5 and call(ws(1, N, 32, 8, d, gamma)) == 5
+    assert call(1 << 30) == 6
+    # calls that pass partials on from one to the other need their own length's
+    step = lambda size, bits: lib.delta_attn_prefill_steps(
+        FAKE, FAKE, FAKE, FAKE, None, 1, N, 32, 8, d, 64, 4, gamma, FAKE + 8, size, None, bits)
+    own = ws(1, N, 32, 8, d, gamma)
+    for bits in (2, 4, 1 | 2, 2 | 8, 4 | 8):
+        assert step(own, bits) == 5 and step(min(size, own - 256), bits) == 6
+    assert step(size, 7) == 5 and step(size, 7 | 8) == 5 and step(size, 1) == 5
+
+
+def test_every_longer_workspace_serves_every_shorter_length(lib):
+    """Lengths around every drop of the chunk count, for several row widths."""
+    ws = lib.da_workspace_bytes
+    lens = sorted({int(1000 * 1.07 ** i) for i in range(110)})
+    for Hq, d, gamma in ((32, 128, 8), (32, 64, 64), (64, 128, 1), (1, 64, 16)):
+        sizes = [ws(1, n, Hq, Hq, d, gamma) for n in lens]
+        for i, n in enumerate(lens):
+            least = min(sizes[i:])
+            assert delta(lib, N=n, Hq=Hq, Hkv=Hq, d=d, gamma=gamma, ws=FAKE + 8, wsz=least) == 5, (n, Hq, d, gamma)
