@@ -279,6 +279,15 @@ void tile_sparse(Args& a, const Problem& P, bool fused) {
   const int64_t ramp = keys < P.N ? keys : P.N;
   const int64_t work = blocks * (2 * (int64_t)P.N - ramp) / (2 * (int64_t)P.N);
   int waves = attn_waves(Launch::kSparseRows, P.d, h8, blocks, work, keys, P.N >= 4 * keys);
+  // Two half-size workgroups share a CU's 160 KB of LDS only if each stages at most
+  // 16 KB of dense rows beside its 64 KB ring: 128 / gamma rows of 512 bytes at
+  // d = 128, so not at gamma 2 (3 does not divide a slab).  There they pay only while
+  // each has a CU to itself.  Whole calls, gamma 2, window 512, 32 heads, 8 -> 4
+  // wavefronts: 1000 tokens 54.2 -> 48.4 us (128 workgroups of eight), 1500 tokens
+  // 64.1 -> 69.6 us (192; window 1024, 125 by work, 73.2 -> 64.9 us), 4096 tokens
+  // 163 -> 185 us, 40000 tokens 7.30 -> 7.67 ms.
+  const bool alone = fused && P.d == 128 && P.gamma > 1 && P.gamma < 4;
+  if (alone && work * 2 > kCUs) waves = kAttnWaves;
   // (a slab of half the rows may hold no whole group, and twice the blocks may
   // pass the grid's limit)
   if (waves < kAttnWaves &&
