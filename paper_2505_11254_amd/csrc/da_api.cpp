@@ -471,7 +471,7 @@ da_status run_delta(const Problem& P, void* workspace, size_t workspace_bytes, v
     a.fuse = corr_mode == DA_CORR_RECOMPUTE ? 2 : 1;
     // One key chunk has nothing to merge: with both steps asked for, the strided
     // kernel writes the dense rows beside their partials (the merge's arithmetic,
-    // one launch less: 1024 tokens, one d 64 head 32.9 -> 29.5 us).  The partials
+    // one launch less: 1024 tokens, one d 64 head 32.9 -> 30.1 us).  The partials
     // stay for a later call that asks for the merge alone.
     const unsigned both = DA_STEP_DENSE_ROWS | DA_STEP_CORRECT;
     const bool direct = plan.nC == 1 && (steps & both) == both;

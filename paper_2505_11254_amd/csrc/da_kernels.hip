@@ -949,50 +949,51 @@ __device__ __forceinline__ void attn_body(const Args& a, uint32_t bid, uint32_t 
     float* const stg = (float*)smem + wave * (16 * D);
     const int rsub = lane / CPR, cc = lane % CPR;
     const int64_t row0 = ((int64_t)b * a.Hq + h) * a.nR_max;
-    // rows of `base`, `stride` floats apart
-    auto store = [&](float* base, int64_t stride) {
-#pragma unroll
-      for (int pass = 0; pass < 2; ++pass) {
-        if (pass) wave_lds_exchange();  // the first pass's reads are done
-        if (row_valid && (col >> 4) == pass) {
-          const int r16 = col & 15;
-#pragma unroll
-          for (int mb = 0; mb < D / 32; ++mb)
-#pragma unroll
-            for (int jq = 0; jq < 4; ++jq)
-              *(f32x4*)(stg + r16 * D + (((8 * mb + 2 * jq + half) ^ (r16 & (CPR - 1))) * 4)) =
-                  f32x4{o[mb][4 * jq], o[mb][4 * jq + 1], o[mb][4 * jq + 2], o[mb][4 * jq + 3]};
-        }
-        wave_lds_exchange();
-        // reads first, then the stores
-        constexpr int NI = 16 / RPI;
-        f32x4 w[NI];
-#pragma unroll
-        for (int i = 0; i < NI; ++i) {
-          const int rr = i * RPI + rsub;
-          w[i] = *(const f32x4*)(stg + rr * D + ((cc ^ (rr & (CPR - 1))) * 4));
-        }
-        const int rb = wr0 + 16 * pass + rsub;
-        float* const prow = base + (row0 + rb) * stride + cc * 4;
-        const int64_t rstep = RPI * stride;
-#pragma unroll
-        for (int i = 0; i < NI; ++i)
-          if (rb + i * RPI < R1) *(f32x4*)(prow + i * rstep) = w[i];
-      }
-    };
-    store(a.part_o + (int64_t)c * D, (int64_t)a.nC * D);
     if (a.merged) {
-      // the only chunk: the merged rows too, with the merge's arithmetic
-      wave_lds_exchange();
+      // the only chunk: normalised rows, with the merge's arithmetic, which are
+      // the merged rows as well (as a partial, each has a normaliser of 1)
       const float inv = 1.f / lt;
 #pragma unroll
       for (int mb = 0; mb < D / 32; ++mb) o[mb] *= inv;
-      store(a.dense, D);
+    }
+#pragma unroll
+    for (int pass = 0; pass < 2; ++pass) {
+      if (pass) wave_lds_exchange();  // the first pass's reads are done
+      if (row_valid && (col >> 4) == pass) {
+        const int r16 = col & 15;
+#pragma unroll
+        for (int mb = 0; mb < D / 32; ++mb)
+#pragma unroll
+          for (int jq = 0; jq < 4; ++jq)
+            *(f32x4*)(stg + r16 * D + (((8 * mb + 2 * jq + half) ^ (r16 & (CPR - 1))) * 4)) =
+                f32x4{o[mb][4 * jq], o[mb][4 * jq + 1], o[mb][4 * jq + 2], o[mb][4 * jq + 3]};
+      }
+      wave_lds_exchange();
+      // reads first, then the stores (row r lies r * nC * D floats past row 0)
+      constexpr int NI = 16 / RPI;
+      f32x4 w[NI];
+#pragma unroll
+      for (int i = 0; i < NI; ++i) {
+        const int rr = i * RPI + rsub;
+        w[i] = *(const f32x4*)(stg + rr * D + ((cc ^ (rr & (CPR - 1))) * 4));
+      }
+      const int rb = wr0 + 16 * pass + rsub;
+      float* const prow = a.part_o + ((row0 + rb) * a.nC + c) * D + cc * 4;
+      const int64_t rstep = (int64_t)RPI * a.nC * D;
+#pragma unroll
+      for (int i = 0; i < NI; ++i)
+        if (rb + i * RPI < R1) *(f32x4*)(prow + i * rstep) = w[i];
+      if (a.merged) {
+        float* const drow = a.dense + (row0 + rb) * D + cc * 4;
+#pragma unroll
+        for (int i = 0; i < NI; ++i)
+          if (rb + i * RPI < R1) *(f32x4*)(drow + i * (RPI * D)) = w[i];
+      }
     }
     if (row_valid && half == 0) {
       const int64_t slot = (row0 + my_r) * a.nC + c;
       a.part_ml[slot * 2] = has_ref ? ref : -INFINITY;  // -inf when no key of the chunk is visible
-      a.part_ml[slot * 2 + 1] = lt;
+      a.part_ml[slot * 2 + 1] = a.merged ? 1.f : lt;
     }
     return;
   }
