@@ -105,8 +105,11 @@ __device__ __forceinline__ Seq seq_of(const Args& a, int b) {
 //    slabs whose windows overlap stay on one L2 (4 heads on 4, window 1000, 100K
 //    tokens, whole call 508 -> 463 us; 16 heads on 4, 128 rows apart, 477 us
 //    without and 489 us with it).  The chunk (a power of two, at most kXcdChunk)
-//    leaves at least four rounds of chunks; blocks past the last whole round of 8
-//    chunks keep their index.
+//    leaves at least four rounds of chunks, 64 in a packed batch, where whole chunks
+//    may lie past the end of their sequence and leave their XCD idle (8 heads on 2,
+//    window 1024, six sequences of 1.7-11.7K tokens, four rounds 270 us, 64 rounds
+//    210 us; 2 heads on 2, window 4096, 1.8-25K tokens 345 -> 291 us); blocks past
+//    the last whole round of 8 chunks keep their index.
 constexpr int kXcdChunk = 64, kXcdSpread = 256;
 __device__ __forceinline__ uint32_t xcd_remap(uint32_t i, uint32_t n, bool contiguous,
                                               int log_chunk) {
@@ -1507,8 +1510,9 @@ void prepare_attn(Args& a, int64_t nblocks) {
   a.fd_sub = make_fastdiv((uint32_t)a.n_sub);
   a.fd_turn = make_fastdiv((uint32_t)a.turn);
   a.xcd_log = 0;
+  const int64_t rounds = a.cu && a.B > 1 ? 64 : 4;
   if (MODE == kSparse && kRowsPerWave * a.ppw * 8 >= kXcdSpread * a.n_hgroups)
-    while ((2 << a.xcd_log) <= kXcdChunk && nblocks >= ((int64_t)4 * 8 * 2 << a.xcd_log)) ++a.xcd_log;
+    while ((2 << a.xcd_log) <= kXcdChunk && nblocks >= (rounds * 8 * 2 << a.xcd_log)) ++a.xcd_log;
 }
 
 // Bytes of the dense rows a sparse workgroup stages for the fused store.
