@@ -24,7 +24,7 @@ def make(lens, Hq, Hkv, d, seed):
 @pytest.mark.parametrize("N,d,params,window", [
     (20000, 64, (0.1, 1.0, 1.0), 2048), (20000, 64, (0.1, 1.0, 1.0), 20000),
     (2100, 128, (20.0, 0.0, 0.0), 900), (2100, 64, (20.0, 0.0, 0.0), 4096),
-    (300, 64, (2e5, 1.0, 1.0), 200)])
+    (300, 64, (2e5, 1.0, 1.0), 200), (60, 64, (2e5, 1.0, 1.0), 40)])
 def test_a_diverging_filter_keeps_the_rows_before_its_first_delta(N, d, params, window):
     """Anchors whose key set is whole have a Delta of exactly zero, and so has the
     filter until the first other anchor: their rows stay the sparse rows bit for bit,
