@@ -1046,9 +1046,8 @@ DA_ATTN_KERNEL(D, NW) void attn_pair_kernel(Args ar, Args as, uint32_t nr, uint3
 // One pass in chunk order with a running max M: chunks with no visible key
 // (max -inf) are skipped, and acc, lsum move to a larger M by 2^(M - Mn).
 // The loads of kU chunks go out before any of them is used.
-template <int D, typename VF>
+template <int D, int kU, typename VF>
 __device__ __forceinline__ VF merge_chunks(const float* po, const f32x2* ml, int nc) {
-  constexpr int kU = 8;
   float M = -INFINITY, lsum = 0.f;
   VF acc = VF{};
   for (int c0 = 0; c0 < nc; c0 += kU) {
@@ -1080,8 +1079,8 @@ __device__ __forceinline__ VF merge_chunks(const float* po, const f32x2* ml, int
 // partials; one thread per four values of a row (a wavefront reads whole rows of
 // one chunk stride), so that even a short sequence's rows give every SIMD
 // several wavefronts: 4021 tokens, 32 heads 13.7 -> 5.2 us, 131K 80 -> 61 us
-// against a workgroup per dense row.
-template <int D, bool DELTA>
+// against a workgroup per dense row.  U: chunks loaded together.
+template <int D, bool DELTA, int U>
 __global__ __launch_bounds__(kEpiThreads) void merge_rows_kernel(Args a) {
   constexpr int V = D / 4;
   const uint32_t n_rows = (uint32_t)a.B * (uint32_t)a.Hq * (uint32_t)a.nR_max;
@@ -1106,7 +1105,7 @@ __global__ __launch_bounds__(kEpiThreads) void merge_rows_kernel(Args a) {
     const int nc = (int)(((int64_t)pos + a.chunk) / a.chunk);  // chunks holding keys 0..pos
     const int64_t slot0 = (int64_t)row * a.nC;
     const f32x4 dense =
-        merge_chunks<D, f32x4>(a.part_o + slot0 * D + dv, (const f32x2*)a.part_ml + slot0, nc);
+        merge_chunks<D, U, f32x4>(a.part_o + slot0 * D + dv, (const f32x2*)a.part_ml + slot0, nc);
     if (!DELTA) {
       *(f32x4*)(a.dense + (int64_t)row * D + dv) = dense;
     } else if (anchor) {
@@ -1166,7 +1165,7 @@ __global__ __launch_bounds__(kEpiThreads) void delta_epilogue_kernel(Args a) {
     const int h = h0 + hh;
     const int64_t slot0 = (((int64_t)b * a.Hq + h) * a.nR_max + r) * a.nC;
     const f32x8 dense =
-        merge_chunks<D, f32x8>(a.part_o + slot0 * D + dc * 8, (const f32x2*)a.part_ml + slot0, nc);
+        merge_chunks<D, 8, f32x8>(a.part_o + slot0 * D + dc * 8, (const f32x2*)a.part_ml + slot0, nc);
     uint16_t* orow = a.out + ((sq.base + pos) * a.Hq + h) * (int64_t)D + dc * 8;
     *(bf16x8_t*)orow = __builtin_convertvector(dense, bf16x8_t);
     if (anchor && EPI == kEpiDelta) {
@@ -1684,13 +1683,22 @@ hipError_t launch_delta_epilogue(const Args& a0, hipStream_t s) {
     if (rows > INT32_MAX) return hipErrorInvalidValue;  // (over a terabyte of partials)
     const int64_t rpb = kEpiThreads / (a.d / 4);
     const dim3 g((unsigned)std::min<int64_t>((rows + rpb - 1) / rpb, 1 << 20));
+#define DA_MERGE(DD, DELTA, U) hipLaunchKernelGGL((merge_rows_kernel<DD, DELTA, U>), g, t, 0, s, a)
+#define DA_MERGE_U(DD, DELTA)                \
+  do {                                       \
+    if (a.nC <= 2) DA_MERGE(DD, DELTA, 2);   \
+    else if (a.nC <= 4) DA_MERGE(DD, DELTA, 4); \
+    else DA_MERGE(DD, DELTA, 8);             \
+  } while (0)
     if (a.d == 128) {
-      if (a.fuse) hipLaunchKernelGGL((merge_rows_kernel<128, false>), g, t, 0, s, a);
-      else hipLaunchKernelGGL((merge_rows_kernel<128, true>), g, t, 0, s, a);
+      if (a.fuse) DA_MERGE_U(128, false);
+      else DA_MERGE_U(128, true);
     } else {
-      if (a.fuse) hipLaunchKernelGGL((merge_rows_kernel<64, false>), g, t, 0, s, a);
-      else hipLaunchKernelGGL((merge_rows_kernel<64, true>), g, t, 0, s, a);
+      if (a.fuse) DA_MERGE_U(64, false);
+      else DA_MERGE_U(64, true);
     }
+#undef DA_MERGE_U
+#undef DA_MERGE
     return hipGetLastError();
   }
   Args a = a0;
