@@ -98,10 +98,11 @@ static int64_t strided_tiles(int64_t B, int64_t N, int Hq, int G, int64_t gamma,
 // prompts up to 3071 tokens 232 -> 212 us.  Against 2 tiles, a minimum of 4
 // takes 29.3 us at 1024 tokens and 8 takes 34.4 us; from 2048 tokens on 2 to 4
 // are alike.  Twice as many chunks cost 5 % where the grid is full already
-// (12000 tokens 154 -> 166 us).  Sequences of at most 448 keys keep one chunk,
-// which needs no merge (300 tokens 25.0 us against 26.7 us in two; 520 tokens
-// 30.8 us against 26.7 us), and so do up to 1024 keys of a problem of a single
-// workgroup.
+// (12000 tokens 154 -> 166 us).  Sequences of at most 320 keys keep one chunk,
+// which needs no merge, however few workgroups that makes.  One chunk -> two and
+// more, whole calls, gamma 64: one d 64 head 300 tokens 17.9 -> 18.2 us, 400 tokens
+// 21.5 -> 19.6 us, 1024 tokens 30.7 -> 20.4 us; 32 heads d 128 300 tokens 24.5 ->
+// 25.4 us, 400 tokens 26.9 -> 24.1 us; 16 heads d 64 18.0 -> 19.3 and 21.4 -> 20.0 us.
 // nC drops only when the partial results would pass kPartialBudget, or, with a nonzero
 // `limit`, until the whole workspace fits `limit` bytes (false when even one
 // chunk does not).  long_chunks: chunks of at least kLongChunk tiles whatever
@@ -118,9 +119,7 @@ bool make_plan(int B, int max_seqlen, int Hq, int Hkv, int d, int gamma, Plan* p
   const int64_t places = B == 1 ? kCUs : kCUs * 3 / 2;
   int64_t min_tiles = (work + places - 1) / places;
   min_tiles = min_tiles < kShortChunk ? kShortChunk : min_tiles > kLongChunk ? kLongChunk : min_tiles;
-  const int hpw = heads_per_block(Hq / Hkv);
-  const bool one_block = (int64_t)B * (Hq / hpw) == 1 && nR_max <= kRowsPerWave * (kAttnWaves / hpw);
-  const int64_t one = one_block ? 1024 : 448;  // keys
+  const int64_t one = 320;  // keys
   const int64_t min_keys = long_chunks ? kKeyTile * kLongChunk
                            : max_seqlen <= one ? one : kKeyTile * min_tiles;
   int64_t nC = (max_seqlen + min_keys - 1) / min_keys;
@@ -471,7 +470,7 @@ da_status run_delta(const Problem& P, void* workspace, size_t workspace_bytes, v
     a.fuse = corr_mode == DA_CORR_RECOMPUTE ? 2 : 1;
     // One key chunk has nothing to merge: with both steps asked for, the strided
     // kernel writes the dense rows beside their partials (the merge's arithmetic,
-    // one launch less: 1024 tokens, one d 64 head 32.9 -> 30.1 us).  The partials
+    // one launch less: 300 tokens, 32 heads, gamma 64 25.4 -> 24.5 us).  The partials
     // stay for a later call that asks for the merge alone.
     const unsigned both = DA_STEP_DENSE_ROWS | DA_STEP_CORRECT;
     const bool direct = plan.nC == 1 && (steps & both) == both;

@@ -57,7 +57,7 @@ def test_a_finer_key_split_costs_no_precision(N, d, window, gamma):
     assert err[1] <= 1.02 * err[0]
 
 
-@pytest.mark.parametrize("N,Hq,Hkv,d", [(300, 8, 2, 128), (448, 1, 1, 64), (40, 4, 4, 64)])
+@pytest.mark.parametrize("N,Hq,Hkv,d", [(300, 8, 2, 128), (320, 1, 1, 64), (40, 4, 4, 64)])
 @pytest.mark.parametrize("first", ["whole", "all steps", "both steps"])
 def test_the_merge_alone_follows_any_call_that_ran_the_strided_rows(N, Hq, Hkv, d, first):
     """One key chunk: the call that needs no merge leaves what a merge on its own
