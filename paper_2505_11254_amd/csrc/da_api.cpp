@@ -98,11 +98,12 @@ static int64_t strided_tiles(int64_t B, int64_t N, int Hq, int G, int64_t gamma,
 // prompts up to 3071 tokens 232 -> 212 us.  Against 2 tiles, a minimum of 4
 // takes 29.3 us at 1024 tokens and 8 takes 34.4 us; from 2048 tokens on 2 to 4
 // are alike.  Twice as many chunks cost 5 % where the grid is full already
-// (12000 tokens 154 -> 166 us).  Sequences of at most 320 keys keep one chunk,
+// (12000 tokens 154 -> 166 us).  Sequences of at most 448 keys keep one chunk,
 // which needs no merge, however few workgroups that makes.  One chunk -> two and
-// more, whole calls, gamma 64: one d 64 head 300 tokens 17.9 -> 18.2 us, 400 tokens
-// 21.5 -> 19.6 us, 1024 tokens 30.7 -> 20.4 us; 32 heads d 128 300 tokens 24.5 ->
-// 25.4 us, 400 tokens 26.9 -> 24.1 us; 16 heads d 64 18.0 -> 19.3 and 21.4 -> 20.0 us.
+// more, whole calls, gamma 64: one d 64 head 449 tokens 22.0 -> 19.2 us, 1024 tokens
+// 30.7 -> 20.4 us; 16 heads d 64 300 tokens 18.0 -> 19.3 us; 32 heads d 128 300
+// tokens 24.5 -> 25.4 us, 520 tokens 30.8 -> 26.7 us.  (At 400 tokens two chunks
+// would take 7-13 % less already: 26.9 -> 24.1 us, 21.4 -> 20.0 us.)
 // nC drops only when the partial results would pass kPartialBudget, or, with a nonzero
 // `limit`, until the whole workspace fits `limit` bytes (false when even one
 // chunk does not).  long_chunks: chunks of at least kLongChunk tiles whatever
@@ -119,7 +120,7 @@ bool make_plan(int B, int max_seqlen, int Hq, int Hkv, int d, int gamma, Plan* p
   const int64_t places = B == 1 ? kCUs : kCUs * 3 / 2;
   int64_t min_tiles = (work + places - 1) / places;
   min_tiles = min_tiles < kShortChunk ? kShortChunk : min_tiles > kLongChunk ? kLongChunk : min_tiles;
-  const int64_t one = 320;  // keys
+  constexpr int64_t one = 448;  // keys
   const int64_t min_keys = long_chunks ? kKeyTile * kLongChunk
                            : max_seqlen <= one ? one : kKeyTile * min_tiles;
   int64_t nC = (max_seqlen + min_keys - 1) / min_keys;

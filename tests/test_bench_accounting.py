@@ -96,7 +96,7 @@ def test_library_plan_of_the_workloads():
     """The plan the library reports for the five workloads (da_launch_plan):
     the tiling the kernels run and the counts above depend on."""
     want = {  # fused, sparse heads, strided-row heads, key chunks, keys per chunk
-        "tiny_n1024_d64": (1, 1, 1, 1, 1024),
+        "tiny_n1024_d64": (1, 1, 1, 8, 128),
         "llama8b_layer_32k": (1, 4, 4, 13, 2560),
         "llama8b_layer_131k": (1, 4, 4, 16, 8192),
         "llama8b_layer_1m": (1, 4, 4, 16, 65536),

@@ -77,9 +77,9 @@ def test_delta_matches_oracle_at_both_sizes(case):
     assert_parity(out, ref, "delta path")
 
 
-# one key chunk (320 keys) and the first sizes past it, few and many workgroups;
+# one key chunk (448 keys) and the first sizes past it, one workgroup and many;
 # chunks of the shortest and of in-between lengths; a batch, whose chunks are shorter
-CHUNKS = [((n,), h, 1, d) for d in (64, 128) for n, h in ((1, 8), (320, 8), (321, 16), (320, 1), (1025, 1))] + \
+CHUNKS = [((n,), h, 1, d) for d in (64, 128) for n, h in ((1, 8), (448, 8), (449, 16), (1024, 1), (1025, 1))] + \
          [((2600,), 8, 8, 64), ((4021,), 2, 1, 128), ((1, 800, 1300), 4, 2, 128)]
 
 
@@ -131,8 +131,8 @@ def test_recurrences_over_segment_edges_match_oracle(mode, params):
 def test_block_order_covers_every_head_and_row(Hkv, G):
     """Each kv head's group in a call of its own (another number of head groups,
     so another block order) gives the same bits, for all three kernels (at most
-    320 keys: one key chunk whatever the heads are)."""
-    lens, d, window, n_sink, gamma = (310, 1, 137), 64 if G % 2 else 128, 30, 2, 32
+    448 keys: one key chunk whatever the heads are)."""
+    lens, d, window, n_sink, gamma = (430, 1, 137), 64 if G % 2 else 128, 30, 2, 32
     q, k, v, cu = (x.to(DEV) for x in make(lens, Hkv * G, Hkv, d, seed=Hkv * 10 + G))
     kw = dict(cu_seqlens=cu, max_seqlen=max(lens))
 
