@@ -258,10 +258,10 @@ void set_tiling(Args& a, int waves, int hpw, int rows) {
   a.n_rtiles = (int)(((int64_t)rows + rpb - 1) / rpb);
 }
 
-// Workgroups of a launch over `rows` rows per (sequence, head) and `split` parts.
-int64_t n_blocks(const Problem& P, int waves, int hpw, int64_t rows, int split) {
-  const int64_t rpb = kRowsPerWave * (waves / hpw);
-  return (int64_t)P.B * (P.Hq / hpw) * split * ((rows + rpb - 1) / rpb);
+// Full-size workgroups of a launch over every row.
+int64_t full_blocks(const Problem& P, int hpw) {
+  const int64_t rpb = kRowsPerWave * (kAttnWaves / hpw);
+  return (int64_t)P.B * (P.Hq / hpw) * ((P.N + rpb - 1) / rpb);
 }
 
 // Tiles the sparse launch; in the fused schedule gamma and the list blocks bind
@@ -275,7 +275,7 @@ void tile_sparse(Args& a, const Problem& P, bool fused) {
   const int h8 = heads(kAttnWaves);
   const int64_t keys = P.blk_ptr ? kListKeys : (int64_t)P.window + P.n_sink;
   // rows before a whole key set grow with their position
-  const int64_t blocks = n_blocks(P, kAttnWaves, h8, P.N, 1);
+  const int64_t blocks = full_blocks(P, h8);
   const int64_t ramp = keys < P.N ? keys : P.N;
   const int64_t work = blocks * (2 * (int64_t)P.N - ramp) / (2 * (int64_t)P.N);
   int waves = attn_waves(Launch::kSparseRows, P.d, h8, blocks, work, keys, P.N >= 4 * keys);
@@ -288,11 +288,8 @@ void tile_sparse(Args& a, const Problem& P, bool fused) {
   // 163 -> 185 us, 40000 tokens 7.30 -> 7.67 ms.
   const bool alone = fused && P.d == 128 && P.gamma > 1 && P.gamma < 4;
   if (alone && work * 2 > kCUs) waves = kAttnWaves;
-  // (a slab of half the rows may hold no whole group, and twice the blocks may
-  // pass the grid's limit)
-  if (waves < kAttnWaves &&
-      (heads(waves) == 0 || n_blocks(P, waves, heads(waves), P.N, 1) > INT32_MAX))
-    waves = kAttnWaves;
+  // (a slab of half the rows may hold no whole group)
+  if (heads(waves) == 0) waves = kAttnWaves;
   set_tiling(a, waves, heads(waves), P.N);
 }
 
@@ -303,9 +300,8 @@ int64_t strided_blocks(const Args& a) { return sparse_blocks(a) * a.nC; }
 void tile_dense(Args& a, const Problem& P) {
   const int G = P.Hq / P.Hkv;
   const int h8 = heads_per_block(G);
-  const int64_t work = n_blocks(P, kAttnWaves, h8, P.N, 1) / 2;
-  int waves = attn_waves(Launch::kDenseCausal, P.d, h8, 2 * work, work, 0, false);
-  if (n_blocks(P, waves, heads_per_block(G, waves), P.N, 1) > INT32_MAX) waves = kAttnWaves;
+  const int64_t work = full_blocks(P, h8) / 2;
+  const int waves = attn_waves(Launch::kDenseCausal, P.d, h8, 2 * work, work, 0, false);
   set_tiling(a, waves, heads_per_block(G, waves), P.N);
 }
 
@@ -314,9 +310,7 @@ void tile_strided(Args& a, const Problem& P, const Plan& plan) {
   const int G = P.Hq / P.Hkv;
   const int64_t tail = P.cu ? (int64_t)plan.nR_max - plan.nA_max : P.N % P.gamma;
   const int64_t work = strided_tiles(P.B, P.N, P.Hq, G, P.gamma, tail) / (plan.chunk / kKeyTile);
-  int waves = attn_waves(Launch::kStridedRows, P.d, heads_per_block(G), work, work, 0, true);
-  if (n_blocks(P, waves, heads_per_block(G, waves), plan.nR_max, plan.nC) > INT32_MAX)
-    waves = kAttnWaves;
+  const int waves = attn_waves(Launch::kStridedRows, P.d, heads_per_block(G), work, work, 0, true);
   set_tiling(a, waves, heads_per_block(G, waves), plan.nR_max);
 }
 

@@ -1529,6 +1529,7 @@ int pre_bytes(const Args& a) {
 template <int MODE>
 hipError_t launch_attn(const Args& a0, hipStream_t s, int64_t nblocks) {
   if (nblocks <= 0) return hipSuccess;
+  if (nblocks > INT32_MAX) return hipErrorInvalidValue;
   Args a = a0;
   prepare_attn<MODE>(a, nblocks);
   const int pre = MODE == kSparse ? pre_bytes(a) : 0;
@@ -1540,8 +1541,10 @@ hipError_t launch_attn(const Args& a0, hipStream_t s, int64_t nblocks) {
     if (waves == 8) DA_ATTN(128, 8);
     else DA_ATTN(128, 4);
   } else {
-    if (waves == 8) DA_ATTN(64, 8);
-    else DA_ATTN(64, 4);
+    // (eight at d = 64: only fused sparse slabs that no half-size workgroup holds)
+    if (waves == 4) DA_ATTN(64, 4);
+    else if constexpr (MODE == kSparse) DA_ATTN(64, 8);
+    else return hipErrorInvalidValue;
   }
 #undef DA_ATTN
   return hipGetLastError();
@@ -1636,7 +1639,9 @@ hipError_t launch_sparse(const Args& a0, hipStream_t s) {
   Args ar = *a0.rows, as = a0;
   const int64_t nr = dense_row_blocks(ar), nr8 = (nr + 7) / 8 * 8;
   const int waves = as.hpw * as.ppw;
-  if (nr <= 0 || ns <= 0 || ar.hpw * ar.ppw != waves || nr8 + ns > INT32_MAX) return hipErrorInvalidValue;
+  if (nr <= 0 || ns <= 0 || ar.hpw * ar.ppw != waves || nr8 + ns > INT32_MAX ||
+      (as.d == 64 && waves != 4))
+    return hipErrorInvalidValue;
   order_dense_rows(ar);
   prepare_attn<kDenseRows>(ar, nr);
   prepare_attn<kSparse>(as, ns);
@@ -1649,8 +1654,7 @@ hipError_t launch_sparse(const Args& a0, hipStream_t s) {
     if (waves == 8) DA_PAIR(128, 8);
     else DA_PAIR(128, 4);
   } else {
-    if (waves == 8) DA_PAIR(64, 8);
-    else DA_PAIR(64, 4);
+    DA_PAIR(64, 4);
   }
 #undef DA_PAIR
   return hipGetLastError();
