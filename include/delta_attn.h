@@ -320,31 +320,54 @@ da_status da_check_inputs(const int32_t* cu_seqlens, int B, int max_seqlen, int 
  * calls (block_q = 64, 128 or 256): a host-only query, no HIP call.  A caller
  * counts the work the kernels execute (whole tiles of key_tile keys by
  * rows_per_wave query rows per wavefront) from these numbers instead of
- * restating the plan.  Each attention workgroup holds waves_per_block
+ * restating the plan.  Each full-size attention workgroup holds waves_per_block
  * wavefronts: heads query heads of one GQA group, each with waves_per_block /
- * heads row sub-tiles of rows_per_wave rows.  (Small launches, short windows
- * and d = 64 run workgroups of half as many wavefronts; each wavefront's rows
- * and tiles are the same.)  The strided dense rows split
- * their key axis into key_chunks chunks of chunk_keys keys.
+ * heads row sub-tiles of rows_per_wave rows.  A launch may take workgroups of
+ * half as many wavefronts, and then other heads (see da_launch_workgroups): every
+ * wavefront's rows and tiles, and so these counts, are the same.  The strided
+ * dense rows split their key axis into key_chunks chunks of chunk_keys keys.
  * Returns DA_ERR_NULL without `plan`, otherwise the status the whole-path
  * call would return for these sizes before touching the device.
  */
 typedef struct {
   int fused;            /* 1: the whole-path call takes the fused schedule */
-  int sparse_heads;     /* query heads per sparse workgroup in that schedule */
-  int rows_heads;       /* query heads per strided-row (and dense causal) workgroup */
+  int sparse_heads;     /* query heads per full-size sparse workgroup in that schedule */
+  int rows_heads;       /* query heads per full-size strided-row (and dense causal) workgroup */
   int key_chunks;       /* key chunks of the strided dense rows */
   int chunk_keys;       /* keys per chunk, a multiple of key_tile */
   int key_tile;         /* keys per tile */
   int rows_per_wave;    /* query rows per wavefront */
-  int waves_per_block;  /* wavefronts per attention workgroup */
-  int sparse_slab_rows; /* rows per query head of a sparse workgroup in that schedule:
+  int waves_per_block;  /* wavefronts per full-size attention workgroup */
+  int sparse_slab_rows; /* rows per query head of a full-size sparse workgroup in that schedule:
                            waves_per_block / sparse_heads * rows_per_wave (a multiple of gamma
                            when fused) */
 } da_plan;
 
 da_status da_launch_plan(int B, int max_seqlen, int Hq, int Hkv, int d, int gamma, int block_q,
                          da_plan* plan);
+
+/*
+ * The workgroups that the attention launches of these sizes take (host only, no
+ * HIP call): wavefronts, waves_per_block of da_launch_plan or half of it, and
+ * query heads per workgroup; a workgroup holds waves / heads row sub-tiles per
+ * head.  packed: 0 for the fixed-length calls, 1 with cu_seqlens.  mode: the
+ * correction (DA_CORR_DELTA for delta_attn_prefill).  block_q: 0, or the block
+ * size of the key-block-list calls (window 1 and n_sink 0 then).  With
+ * da_workspace_bytes() of workspace or more, where it matters.
+ * Returns DA_ERR_NULL without `w`, otherwise the status the whole-path call would
+ * return for these sizes before touching the device.
+ */
+typedef struct {
+  int sparse_waves, sparse_heads; /* sparse rows of the whole-path call */
+  int rows_waves, rows_heads;     /* its strided dense rows */
+  int together;                   /* 1: one launch runs both */
+  int base_waves, base_heads;     /* sparse_attn_prefill, blocksparse_attn_prefill */
+  int dense_waves, dense_heads;   /* dense_causal_attn_prefill */
+} da_workgroups;
+
+da_status da_launch_workgroups(int B, int max_seqlen, int packed, int Hq, int Hkv, int d,
+                               int window, int n_sink, int gamma, int block_q, int mode,
+                               da_workgroups* w);
 
 /* Static, NUL-terminated name of a status code. */
 const char* da_status_string(da_status s);

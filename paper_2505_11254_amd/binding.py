@@ -49,6 +49,15 @@ class Plan(ctypes.Structure):
         return {n: int(getattr(self, n)) for n, _ in self._fields_}
 
 
+class Workgroups(ctypes.Structure):
+    """da_workgroups of include/delta_attn.h: the workgroups the launches take."""
+    _fields_ = [(n, ctypes.c_int) for n in ("sparse_waves", "sparse_heads", "rows_waves",
+                                            "rows_heads", "together", "base_waves", "base_heads",
+                                            "dense_waves", "dense_heads")]
+
+    as_dict = Plan.as_dict
+
+
 class DeltaAttnError(RuntimeError):
     def __init__(self, fn, status, hip_error=0):
         self.status = status
@@ -98,6 +107,8 @@ def load_library(path: str = LIB_PATH, check_abi: bool = True):
     lib.da_abi_version.restype = ctypes.c_int
     lib.da_launch_plan.argtypes = [ctypes.c_int] * 7 + [ctypes.POINTER(Plan)]
     lib.da_launch_plan.restype = ctypes.c_int
+    lib.da_launch_workgroups.argtypes = [ctypes.c_int] * 11 + [ctypes.POINTER(Workgroups)]
+    lib.da_launch_workgroups.restype = ctypes.c_int
     if check_abi and lib.da_abi_version() != ABI_VERSION:
         raise RuntimeError(f"{path} has ABI version {lib.da_abi_version()}, this binding needs "
                            f"{ABI_VERSION}: rebuild it with __graft_entry__.build()")
@@ -197,13 +208,24 @@ def workspace_bytes(B, max_seqlen, Hq, Hkv, d, gamma) -> int:
 
 
 def launch_plan(B, max_seqlen, Hq, Hkv, d, gamma, block_q=0) -> dict:
-    """The library's tiling of a problem (da_launch_plan; host only)."""
+    """The library's tiling of a problem in full-size workgroups (da_launch_plan; host only)."""
     p = Plan()
     lib = load_library()
     rc = lib.da_launch_plan(B, max_seqlen, Hq, Hkv, d, gamma, block_q, ctypes.byref(p))
     if rc != 0:
         raise DeltaAttnError("da_launch_plan", rc)
     return p.as_dict()
+
+
+def launch_workgroups(B, max_seqlen, Hq, Hkv, d, gamma, *, window=1, n_sink=0, block_q=0, mode=0,
+                      packed=False) -> dict:
+    """The workgroups that the launches of a problem take (da_launch_workgroups; host only)."""
+    w = Workgroups()
+    rc = load_library().da_launch_workgroups(B, max_seqlen, int(packed), Hq, Hkv, d, window, n_sink,
+                                             gamma, block_q, mode, ctypes.byref(w))
+    if rc != 0:
+        raise DeltaAttnError("da_launch_workgroups", rc)
+    return w.as_dict()
 
 
 def fused_supported(Hq, Hkv, gamma) -> bool:

@@ -314,6 +314,15 @@ void tile_strided(Args& a, const Problem& P, const Plan& plan) {
   set_tiling(a, waves, heads_per_block(G, waves), plan.nR_max);
 }
 
+// Whether the unfused schedule runs the sparse rows `as` and the strided rows `ar`
+// in one launch: up to 40 rounds of the CUs (where it pays: see attn_pair_kernel)
+// and where they take workgroups of one size.
+bool paired(const Args& as, const Args& ar) {
+  return as.hpw * as.ppw == ar.hpw * ar.ppw &&
+         sparse_blocks(as) * as.hpw * as.ppw <= 40 * kCUs * kAttnWaves &&
+         strided_blocks(ar) < INT32_MAX / 2;
+}
+
 Args base_args(const Problem& P) {
   Args a;
   memset(&a, 0, sizeof a);
@@ -492,11 +501,7 @@ da_status run_delta(const Problem& P, void* workspace, size_t workspace_bytes, v
   tile_sparse(as, P, false);
   tile_strided(ar, P, plan);
   const unsigned both = DA_STEP_SPARSE | DA_STEP_DENSE_ROWS;
-  // one launch for both, up to 40 rounds of the CUs (where it pays: see
-  // attn_pair_kernel) and where they take workgroups of one size
-  const bool pair = (steps & both) == both && as.hpw * as.ppw == ar.hpw * ar.ppw &&
-                    sparse_blocks(as) * as.hpw * as.ppw <= 40 * kCUs * kAttnWaves &&
-                    strided_blocks(ar) < INT32_MAX / 2;
+  const bool pair = (steps & both) == both && paired(as, ar);
   if (pair) as.rows = &ar;
   // Step 1: sparse attention for every row (+ fp32 copy at anchors).
   if (steps & DA_STEP_SPARSE) {
@@ -666,6 +671,42 @@ da_status da_launch_plan(int B, int max_seqlen, int Hq, int Hkv, int d, int gamm
   plan->key_tile = da::kKeyTile;
   plan->rows_per_wave = da::kRowsPerWave;
   plan->waves_per_block = da::kAttnWaves;
+  return DA_OK;
+}
+
+da_status da_launch_workgroups(int B, int max_seqlen, int packed, int Hq, int Hkv, int d,
+                               int window, int n_sink, int gamma, int block_q, int mode,
+                               da_workgroups* w) {
+  if (!w) return DA_ERR_NULL;
+  if (packed < 0 || packed > 1 || block_q < 0) return DA_ERR_PARAM;
+  if (mode < DA_CORR_DELTA || mode > DA_CORR_ABG) return DA_ERR_PARAM;
+  alignas(16) static const int32_t given[4] = {};  // stands for every tensor
+  Problem P{given, given, given, const_cast<int32_t*>(given), packed ? given : nullptr, B,
+            max_seqlen, Hq, Hkv, d, window, n_sink, gamma};
+  if (block_q) P.blk_ptr = P.blk_idx = given;
+  P.block_q = block_q;
+  const da_status st = da::validate(P, true, true);
+  if (st != DA_OK) return st;
+  da::Plan plan;
+  if (!da::make_plan(B, max_seqlen, Hq, Hkv, d, gamma, &plan)) return DA_ERR_SHAPE;
+  const bool fused = mode <= DA_CORR_RECOMPUTE &&
+                     da::fused_heads_per_block(Hq / Hkv, gamma, block_q ? block_q : INT32_MAX) > 0;
+  da::Args as = da::base_args(P), ar, base, dense;
+  as.nC = plan.nC;
+  ar = base = dense = as;
+  da::tile_sparse(as, P, fused);
+  da::tile_strided(ar, P, plan);
+  da::tile_sparse(base, P, false);
+  da::tile_dense(dense, P);
+  w->sparse_waves = as.hpw * as.ppw;
+  w->sparse_heads = as.hpw;
+  w->rows_waves = ar.hpw * ar.ppw;
+  w->rows_heads = ar.hpw;
+  w->together = !fused && da::paired(as, ar);
+  w->base_waves = base.hpw * base.ppw;
+  w->base_heads = base.hpw;
+  w->dense_waves = dense.hpw * dense.ppw;
+  w->dense_heads = dense.hpw;
   return DA_OK;
 }
 

@@ -238,6 +238,38 @@ def test_launch_plan_validates_and_answers_without_a_gpu(lib):
         assert lib.da_launch_plan(*args, ctypes.byref(p)) == status, args
 
 
+def test_launch_workgroups_name_the_launches_that_run(lib):
+    """The workgroups of the calls, which the full-size tiling of da_launch_plan no longer
+    tells: half-size ones at d 64 (with four heads where the plan says eight), in
+    small launches and for short key sets; one launch for both row sets or two."""
+    from paper_2505_11254_amd import binding
+    f = binding.launch_workgroups
+    llama = dict(window=2048, n_sink=64)
+    w = f(1, 1024, 1, 1, 64, 16, window=128, n_sink=4)
+    assert (w["sparse_waves"], w["rows_waves"], w["base_waves"], w["dense_waves"]) == (4, 4, 4, 4)
+    w = f(1, 4096, 8, 1, 64, 32, **llama)
+    assert binding.launch_plan(1, 4096, 8, 1, 64, 32)["sparse_heads"] == 8
+    assert (w["sparse_heads"], w["rows_heads"], w["base_heads"], w["dense_heads"]) == (4, 4, 4, 4)
+    w = f(1, 131072, 32, 8, 128, 64, **llama)
+    assert w == dict(sparse_waves=8, sparse_heads=4, rows_waves=8, rows_heads=4, together=0,
+                     base_waves=8, base_heads=4, dense_waves=8, dense_heads=4)
+    assert f(1, 131072, 32, 8, 128, 64, window=128)["sparse_waves"] == 4
+    assert f(1, 131072, 32, 8, 128, 64, block_q=64)["sparse_waves"] == 8
+    # gamma 256 fits a full-size slab of one head only (at d 64, too)
+    assert f(1, 131072, 32, 8, 64, 256, **llama)["sparse_waves"] == 8
+    # the moving average runs unfused: in one launch up to 40 rounds of the CUs
+    assert [f(1, n, 32, 8, 128, 64, mode=3, **llama)["together"] for n in (32768, 131072)] == [1, 0]
+    p = binding.Workgroups()
+    ok = (1, 1024, 0, 4, 2, 64, 16, 0, 8, 0, 0)
+    assert lib.da_launch_workgroups(*ok, ctypes.byref(p)) == 0
+    assert lib.da_launch_workgroups(*ok, None) == 1
+    for i, v, status in [(0, 0, 2), (4, 3, 2), (5, 96, 4), (6, 0, 3), (7, -1, 3), (8, 0, 3),
+                         (9, 32, 3), (9, 64, 4), (10, 5, 3), (2, 2, 3)]:
+        args = list(ok)
+        args[i] = v
+        assert lib.da_launch_workgroups(*args, ctypes.byref(p)) == status, (i, v)
+
+
 def test_noalloc_call_validates_and_bounds_its_scratch_before_the_gpu(lib):
     """The allocation-free entry point rejects bad arguments like the others,
     and a problem whose workspace cannot fit its static array (even with one
