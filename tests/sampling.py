@@ -10,7 +10,7 @@ from __future__ import annotations
 import numpy as np
 import torch
 
-# spec tolerances for bf16 I/O with fp32 accumulation
+# parity tolerances for bf16 I/O with fp32 accumulation
 MAX_ABS = 2e-2
 MEAN_ABS = 2e-3
 
@@ -100,3 +100,23 @@ def assert_parity(got, ref, what="", max_abs=MAX_ABS, mean_abs=MEAN_ABS, slack=N
 def to_oracle_bits(t: torch.Tensor) -> np.ndarray:
     """bf16 tensor (any device) -> uint16 numpy bit patterns the oracle widens exactly."""
     return t.detach().contiguous().view(torch.int16).cpu().numpy().view(np.uint16)
+
+
+def least_workspace(B, N, Hq, Hkv, d, gamma):
+    """The least workspace that a packed delta_attn_prefill of these sizes takes, asked of
+    the library.  (The size is looked at before the alignment, so a misaligned workspace
+    tells an accepted size from a refused one without a launch.)"""
+    from paper_2505_11254_amd import binding
+    lib, at = binding.load_library(), 1 << 20
+    status = lambda size: lib.delta_attn_prefill_varlen(at, at, at, at, at, B, N, Hq, Hkv, d, 64, 4,
+                                                        gamma, at + 8, size, None)
+    names = binding.STATUS
+    lo, hi = 0, binding.workspace_bytes(B, N, Hq, Hkv, d, gamma)  # refused, accepted
+    assert names[status(hi)] == "DA_ERR_ALIGN" and names[status(lo)] == "DA_ERR_WORKSPACE"
+    while hi - lo > 1:
+        mid = (lo + hi) // 2
+        if names[status(mid)] == "DA_ERR_ALIGN":
+            hi = mid
+        else:
+            lo = mid
+    return hi

@@ -7,7 +7,7 @@ import pytest
 import torch
 
 import oracle
-from sampling import to_oracle_bits
+from sampling import least_workspace, to_oracle_bits
 
 pytestmark = pytest.mark.gpu
 
@@ -24,14 +24,6 @@ def make(lens, Hq, Hkv, d, seed):
     return random_qkv(lens, Hq, Hkv, d, seed, device="cpu")
 
 
-def long_chunk_bytes(N, Hq, d, gamma):
-    """Workspace of one sequence whose key chunks hold at least 2560 keys."""
-    up = lambda x: (x + 255) // 256 * 256
-    rows = Hq * (N // gamma + min(gamma - 1, N))
-    n = -(-N // 2560)
-    return up(rows * d * 4) + up(rows * n * d * 4) + up(rows * n * 2 * 4)
-
-
 @pytest.mark.parametrize("N,d,window,gamma", [(2500, 128, 1024, 64), (2500, 64, 1024, 32), (4021, 128, 2048, 64)])
 def test_a_finer_key_split_costs_no_precision(N, d, window, gamma):
     """Corrected rows against the 64-bit oracle, long key chunks and the 16 that the
@@ -46,7 +38,7 @@ def test_a_finer_key_split_costs_no_precision(N, d, window, gamma):
     pos = np.arange(N)
     rows = (pos - pos % gamma >= window + n_sink) & (pos % gamma != 0) & (pos < N // gamma * gamma)
     full = B().workspace_bytes(1, N, Hq, Hkv, d, gamma)
-    least = long_chunk_bytes(N, Hq, d, gamma)
+    least = least_workspace(1, N, Hq, Hkv, d, gamma)
     assert full > 3 * least
     err = []
     for size in (least, full):
@@ -90,7 +82,7 @@ def test_steps_agree_on_the_layout_whatever_smaller_workspace_each_is_given(fuse
     b = B()
     q, k, v, _ = (x.to(DEV) for x in make((N,), Hq, Hkv, d, seed=N))
     kw = dict(window=100, n_sink=3, gamma=gamma)
-    full, least = b.workspace_bytes(1, N, Hq, Hkv, d, gamma), long_chunk_bytes(N, Hq, d, gamma)
+    full, least = b.workspace_bytes(1, N, Hq, Hkv, d, gamma), least_workspace(1, N, Hq, Hkv, d, gamma)
     middle = (least + full) // 512 * 256
     ws = torch.empty(full, dtype=torch.uint8, device=DEV)
     F = b.STEP_FUSED if fused else 0
