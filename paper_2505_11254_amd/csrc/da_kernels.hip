@@ -1227,57 +1227,49 @@ __global__ __launch_bounds__(kEpiThreads) void delta_epilogue_kernel(Args a) {
 // the EMA).  A diverging filter's A^(segment) may pass the range of floats, and a
 // state may stop being finite; times the exact zeros of covered anchors, or of A,
 // that would make NaN of rows whose correction is finite.  Such channels take their
-// steps in order, one thread each, and so do those of at most kScanSegs anchors,
-// whose 64 entry states are the longer chain (whole calls, 32 heads, filter: 16
-// anchors 31.0 -> 25.3 us, 64 anchors 36.5 -> 33.5 us, 128 anchors 44.9 -> 46.8 us;
-// four sequences of 11-135 tokens, gamma 7 42.5 -> 28.8 us, 50.2 us with registers
-// for one workgroup per CU instead of two).
+// steps in order, one thread each, and so do the sequences of at most kScanSegs
+// anchors in a longer batch, whose 64 entry states are the longer chain (whole
+// calls, four sequences of 11-135 tokens, 32 heads, gamma 7, filter 42.5 -> 28.8 us,
+// 50.2 us with registers for one workgroup per CU instead of two).
 constexpr int kScanCh = 16, kScanSegs = 64;
 constexpr double kScanMaxPower = 1e30;  // largest entry of A^(segment) that segments take
 template <int CORR>
-__global__ __launch_bounds__(kScanCh * kScanSegs) __attribute__((amdgpu_waves_per_eu(8)))
-void corr_scan_kernel(Args a, int64_t block0) {
-  constexpr int S = CORR == 3 ? 1 : 3;  // state size
-  __shared__ float st[kScanSegs][S][kScanCh];
-  __shared__ float Ap[S * S];
-  __shared__ int in_order;  // 1: no segments
-  const int cl = threadIdx.x % kScanCh, seg = threadIdx.x / kScanCh;
-  const int64_t ch0 = (block0 + blockIdx.x) * kScanCh;
-  const int64_t per_seq = (int64_t)a.Hq * a.d;
-  const int b = (int)(ch0 / per_seq);
-  const int h = (int)((ch0 % per_seq) / a.d);
-  const int c = (int)(ch0 % a.d) + cl;
-  const int nA = seq_of(a, b).L / a.gamma;
-  if (nA == 0) return;  // uniform over the block
-  const int64_t base = ((int64_t)b * a.Hq + h) * a.nA_max * a.d + c;
-  float* const dl = a.dbuf + base;
-  float* const ein = CORR == 3 ? a.ebuf + base : nullptr;
+struct Scan {
+  static constexpr int S = CORR == 3 ? 1 : 3;  // state size
   // the filter's state is Delta_0 at anchor 0: its steps start at anchor 1
-  const int first = CORR == 3 ? 0 : 1;
-  const int len = (nA - first + kScanSegs - 1) / kScanSegs;
-  const int i0 = min(nA, first + seg * len), i1 = min(nA, i0 + len);
-
+  static constexpr int first = CORR == 3 ? 0 : 1;
   float A[S][S], g[S];
-  if constexpr (CORR == 3) {
-    const float q = 1.f - a.corr_p[0];
-    A[0][0] = (q == 0.f) ? 0.f : fast_exp2((float)a.gamma * __log2f(q));
-    g[0] = 1.f - A[0][0];
-  } else {
-    // x_i = A x_{i-1} + g Delta_i, A = (I - g h) F: the constant-acceleration
-    // transition F (unit step) followed by the correction of the observed
-    // position (h = (1, 0, 0)) with gain g
-    const float g0 = a.corr_p[0], g1 = a.corr_p[1], g2 = a.corr_p[2];
-    const float F[3][3] = {{1.f - g0, 1.f - g0, 0.5f * (1.f - g0)},
-                           {-g1, 1.f - g1, 1.f - 0.5f * g1},
-                           {-g2, -g2, 1.f - 0.5f * g2}};
+  float *dl, *ein;  // one channel's Delta_i, and its EMA values entering group i
+  int64_t stride;
+
+  // channel `ch` of all (sequence, head, d); nA: the sequence's anchors
+  __device__ __forceinline__ Scan(const Args& a, int64_t ch, int& nA) : stride(a.d) {
+    const int64_t bh = ch / a.d;
+    nA = seq_of(a, (int)(bh / a.Hq)).L / a.gamma;
+    const int64_t base = bh * a.nA_max * a.d + ch % a.d;
+    dl = a.dbuf + base;
+    ein = CORR == 3 ? a.ebuf + base : nullptr;
+    if constexpr (CORR == 3) {
+      const float q = 1.f - a.corr_p[0];
+      A[0][0] = (q == 0.f) ? 0.f : fast_exp2((float)a.gamma * __log2f(q));
+      g[0] = 1.f - A[0][0];
+    } else {
+      // x_i = A x_{i-1} + g Delta_i, A = (I - g h) F: the constant-acceleration
+      // transition F (unit step) followed by the correction of the observed
+      // position (h = (1, 0, 0)) with gain g
+      const float g0 = a.corr_p[0], g1 = a.corr_p[1], g2 = a.corr_p[2];
+      const float F[3][3] = {{1.f - g0, 1.f - g0, 0.5f * (1.f - g0)},
+                             {-g1, 1.f - g1, 1.f - 0.5f * g1},
+                             {-g2, -g2, 1.f - 0.5f * g2}};
 #pragma unroll
-    for (int i = 0; i < 3; ++i) {
-      g[i] = a.corr_p[i];
+      for (int i = 0; i < 3; ++i) {
+        g[i] = a.corr_p[i];
 #pragma unroll
-      for (int j = 0; j < 3; ++j) A[i][j] = F[i][j];
+        for (int j = 0; j < 3; ++j) A[i][j] = F[i][j];
+      }
     }
   }
-  auto step = [&](float* x, float v) {
+  __device__ __forceinline__ void step(float* x, float v) const {
     float y[S];
 #pragma unroll
     for (int i = 0; i < S; ++i) {
@@ -1287,31 +1279,58 @@ void corr_scan_kernel(Args a, int64_t block0) {
     }
 #pragma unroll
     for (int i = 0; i < S; ++i) x[i] = y[i];
-  };
+  }
   // runs the anchors [i0, i1) from state x: batches of kB loads go out together
-  constexpr int kB = 16;
-  auto run = [&](float* x, int i0, int i1, bool store) {
+  __device__ __forceinline__ void run(float* x, int i0, int i1, bool store) const {
+    constexpr int kB = 16;
     for (int i = i0; i < i1; i += kB) {
       float buf[kB];
 #pragma unroll
-      for (int j = 0; j < kB; ++j) buf[j] = dl[(int64_t)min(i + j, i1 - 1) * a.d];
+      for (int j = 0; j < kB; ++j) buf[j] = dl[(int64_t)min(i + j, i1 - 1) * stride];
 #pragma unroll
       for (int j = 0; j < kB; ++j) {
         if (i + j >= i1) break;
-        if (CORR == 3 && store) ein[(int64_t)(i + j) * a.d] = x[0];
+        if (CORR == 3 && store) ein[(int64_t)(i + j) * stride] = x[0];
         step(x, buf[j]);
-        if (CORR == 4 && store) dl[(int64_t)(i + j) * a.d] = x[0];
+        if (CORR == 4 && store) dl[(int64_t)(i + j) * stride] = x[0];
       }
     }
-  };
-
-  auto run_in_order = [&]() {
-    if (seg != 0) return;
+  }
+  __device__ __forceinline__ void run_in_order(int nA) const {
     float x[S] = {};
     x[0] = dl[0];
     run(x, first, nA, true);
-  };
-  if (nA <= kScanSegs) return run_in_order();  // uniform over the block
+  }
+};
+
+// One thread per channel, in order (see scan_in_order).
+template <int CORR>
+__global__ __launch_bounds__(256) void corr_scan_in_order_kernel(Args a, int64_t block0) {
+  const int64_t ch = (block0 + blockIdx.x) * 256 + threadIdx.x;
+  if (ch >= (int64_t)a.B * a.Hq * a.d) return;
+  int nA;
+  const Scan<CORR> scan(a, ch, nA);
+  if (nA > 0) scan.run_in_order(nA);
+}
+
+template <int CORR>
+__global__ __launch_bounds__(kScanCh * kScanSegs) __attribute__((amdgpu_waves_per_eu(8)))
+void corr_scan_kernel(Args a, int64_t block0) {
+  constexpr int S = Scan<CORR>::S, first = Scan<CORR>::first;
+  __shared__ float st[kScanSegs][S][kScanCh];
+  __shared__ float Ap[S * S];
+  __shared__ int in_order;  // 1: no segments
+  const int cl = threadIdx.x % kScanCh, seg = threadIdx.x / kScanCh;
+  int nA;
+  const Scan<CORR> scan(a, (block0 + blockIdx.x) * kScanCh + cl, nA);
+  if (nA == 0) return;  // uniform over the block
+  const int len = (nA - first + kScanSegs - 1) / kScanSegs;
+  const int i0 = min(nA, first + seg * len), i1 = min(nA, i0 + len);
+
+  if (nA <= kScanSegs) {  // uniform over the block
+    if (seg == 0) scan.run_in_order(nA);
+    return;
+  }
   if (threadIdx.x == kScanCh * kScanSegs - 1) {
     // A^len by repeated squaring, in 64 bits (a marginally stable filter's
     // powers cancel); entries stay finite, as products end past kScanMaxPower
@@ -1319,7 +1338,7 @@ void corr_scan_kernel(Args a, int64_t block0) {
     for (int i = 0; i < S; ++i)
       for (int j = 0; j < S; ++j) {
         P[i][j] = i == j ? 1.0 : 0.0;
-        Q[i][j] = A[i][j];
+        Q[i][j] = scan.A[i][j];
       }
     bool fits;
     double sum = 0.0;
@@ -1350,13 +1369,13 @@ void corr_scan_kernel(Args a, int64_t block0) {
     in_order = !fits;
   }
   float x[S] = {};
-  run(x, i0, i1, false);
+  scan.run(x, i0, i1, false);
 #pragma unroll
   for (int i = 0; i < S; ++i) st[seg][i][cl] = x[i];
   __syncthreads();
   if (seg == 0 && !in_order) {
     float e[S] = {};
-    e[0] = dl[0];
+    e[0] = scan.dl[0];
     for (int sg = 0; sg < kScanSegs; ++sg) {
       float y[S];
 #pragma unroll
@@ -1373,10 +1392,13 @@ void corr_scan_kernel(Args a, int64_t block0) {
     if ((__float_as_uint(e[0]) & 0x7f800000u) == 0x7f800000u) in_order = 1;
   }
   __syncthreads();
-  if (in_order) return run_in_order();  // uniform over the block
+  if (in_order) {  // uniform over the block
+    if (seg == 0) scan.run_in_order(nA);
+    return;
+  }
 #pragma unroll
   for (int i = 0; i < S; ++i) x[i] = st[seg][i][cl];
-  run(x, i0, i1, true);
+  scan.run(x, i0, i1, true);
 }
 
 // Adds the per-row correction of a smoothing variant to the gamma rows of one
@@ -1724,23 +1746,40 @@ hipError_t launch_delta_epilogue(const Args& a0, hipStream_t s) {
   return hipGetLastError();
 }
 
+// Whether every channel takes its steps in order, one thread each: for few anchors,
+// where the chain over the segments' entry states is the longer one, and for so
+// many channels that one thread each fills the chip, where a second pass over the
+// anchors only costs.  Measured on an MI355X, whole calls, segments -> in order:
+// 4096 channels 73 anchors 68.4 -> 65.8 us, 151 anchors 53.1 -> 56.2 us; 16384
+// channels 207 anchors 581 -> 578 us, 1076 anchors 4735 -> 4776 us; 32768 channels,
+// 1667 anchors 5351 -> 5342 us; 40960, 2502 anchors 7103 -> 6882 us; 229376, up to
+// 679 anchors 1429 -> 1240 us.
+static bool scan_in_order(int64_t channels, int nA) {
+  return nA <= kScanSegs || channels >= 32768 || nA <= channels / 64;
+}
+
 // After the merge: the scan (EMA, filter) and the apply pass of
 // the smoothing variants (modes 2-4).
 hipError_t launch_correction(const Args& a0, hipStream_t s) {
   Args a = a0;
   if (a.corr_mode < 2) return hipSuccess;
   if (a.corr_mode >= 3) {
-    // (a dispatch holds fewer than 2^32 threads: 65536 (sequence, head) pairs of 64
-    // channels go in one launch of 2^28)
-    constexpr int64_t kMaxBlocks = 1 << 18;
-    const int64_t blocks = (int64_t)a.B * a.Hq * a.d / kScanCh;
-    const dim3 t(kScanCh * kScanSegs);
-    for (int64_t b0 = 0; b0 < blocks; b0 += kMaxBlocks) {
-      const dim3 g((unsigned)std::min(kMaxBlocks, blocks - b0));
-      if (a.corr_mode == 3)
-        hipLaunchKernelGGL(corr_scan_kernel<3>, g, t, 0, s, a, b0);
+    const int64_t channels = (int64_t)a.B * a.Hq * a.d;
+    const bool in_order = scan_in_order(channels, a.nA_max);
+    const int per_block = in_order ? 256 : kScanCh;
+    const int64_t blocks = (channels + per_block - 1) / per_block;
+    // (a dispatch holds fewer than 2^32 threads)
+    const int64_t max_blocks = (int64_t)(1 << 28) / (in_order ? 256 : kScanCh * kScanSegs);
+    for (int64_t b0 = 0; b0 < blocks; b0 += max_blocks) {
+      const dim3 g((unsigned)std::min(max_blocks, blocks - b0));
+      if (in_order && a.corr_mode == 3)
+        hipLaunchKernelGGL(corr_scan_in_order_kernel<3>, g, dim3(256), 0, s, a, b0);
+      else if (in_order)
+        hipLaunchKernelGGL(corr_scan_in_order_kernel<4>, g, dim3(256), 0, s, a, b0);
+      else if (a.corr_mode == 3)
+        hipLaunchKernelGGL(corr_scan_kernel<3>, g, dim3(kScanCh * kScanSegs), 0, s, a, b0);
       else
-        hipLaunchKernelGGL(corr_scan_kernel<4>, g, t, 0, s, a, b0);
+        hipLaunchKernelGGL(corr_scan_kernel<4>, g, dim3(kScanCh * kScanSegs), 0, s, a, b0);
       const hipError_t e = hipGetLastError();
       if (e != hipSuccess) return e;
     }

@@ -1,8 +1,12 @@
 """The recurrences of the smoothing corrections where they leave the usual range."""
 from __future__ import annotations
 
+import numpy as np
 import pytest
 import torch
+
+import oracle
+from sampling import to_oracle_bits
 
 pytestmark = pytest.mark.gpu
 
@@ -56,3 +60,24 @@ def test_more_channels_than_one_launch_takes(mode, params):
         some = B().delta_attn_prefill_correction(*(x[part].contiguous() for x in (q, k, v)), B=16, **kw)
         torch.cuda.synchronize()
         assert torch.equal(out[part], some), b0
+
+
+# (lens, heads, gamma): channels (64 per sequence and head) around the lines between
+# one thread per channel and segments: 64 anchors, a 64th of the channels, 32768 channels;
+# a number of channels that is no multiple of a workgroup's 256
+@pytest.mark.parametrize("lens,Hq,gamma", [((128,), 1, 2), ((130,), 1, 2), ((258,), 128, 2), ((256, 7), 64, 2),
+                                           ((170, 9, 0, 64, 131, 66, 140, 1), 64, 1)])
+@pytest.mark.parametrize("mode,params", [(3, (0.3, 0.0, 0.0)), (4, (0.2, 5e-2, 3.5e-3))])
+def test_scans_in_order_and_in_segments_match_the_oracle(lens, Hq, gamma, mode, params):
+    from paper_2505_11254_amd.inputs import random_qkv
+    q, k, v, cu = random_qkv(lens, Hq, 1, 64, seed=len(lens) + Hq, device="cpu")
+    kw = dict(window=9, n_sink=1, gamma=gamma, mode=mode, params=params)
+    out = B().delta_attn_prefill_correction(*(x.to(DEV) for x in (q, k, v)), cu_seqlens=cu.to(DEV),
+                                            max_seqlen=max(lens), **kw)
+    torch.cuda.synchronize()
+    ref = oracle.delta_attention_variant(*(to_oracle_bits(x) for x in (q, k, v)), cu.numpy().astype(np.int64), **kw)
+    # (a window of 9 keys leaves outputs of O(1): their bf16 rounding, twice in this
+    # schedule, comes on top of the parity bound)
+    err = np.abs(out.float().cpu().numpy().astype(np.float64) - ref)
+    assert (err <= 2e-2 + 2 * np.abs(ref) * 2.0 ** -8).all(), err.max()
+    assert err.mean() <= 2e-3 + np.abs(ref).mean() * 2.0 ** -8
