@@ -1079,7 +1079,7 @@ __device__ __forceinline__ VF merge_chunks(const float* po, const f32x2* ml, int
 // partials; one thread per four values of a row (a wavefront reads whole rows of
 // one chunk stride), so that even a short sequence's rows give every SIMD
 // several wavefronts: 4021 tokens, 32 heads 13.7 -> 5.2 us, 131K 80 -> 61 us
-// against a workgroup per dense row.  U: chunks loaded together.
+// against a workgroup per dense row.  U: chunks loaded together (see launch_delta_epilogue).
 template <int D, bool DELTA, int U>
 __global__ __launch_bounds__(kEpiThreads) void merge_rows_kernel(Args a) {
   constexpr int V = D / 4;
@@ -1709,11 +1709,17 @@ hipError_t launch_delta_epilogue(const Args& a0, hipStream_t s) {
     if (rows > INT32_MAX) return hipErrorInvalidValue;  // (over a terabyte of partials)
     const int64_t rpb = kEpiThreads / (a.d / 4);
     const dim3 g((unsigned)std::min<int64_t>((rows + rpb - 1) / rpb, 1 << 20));
+    // Chunks whose loads go out together: at most those there are.  A row at half the
+    // length has half of the chunks, so from five to eight of them two steps of four
+    // load less for nothing, where bytes and not latency bound the pass: 16 heads,
+    // three prompts of up to 13K tokens, gamma 4 (5M threads) 698 -> 691 us, 32 heads, up
+    // to 11K, gamma 2 1153 -> 1126 us; 40000 tokens, 8 heads, gamma 16 (0.6M) 425 -> 429 us.
+    const bool four = a.nC <= 4 || (a.nC <= 8 && rows * (a.d / 4) >= (1 << 21));
 #define DA_MERGE(DD, DELTA, U) hipLaunchKernelGGL((merge_rows_kernel<DD, DELTA, U>), g, t, 0, s, a)
 #define DA_MERGE_U(DD, DELTA)                \
   do {                                       \
     if (a.nC <= 2) DA_MERGE(DD, DELTA, 2);   \
-    else if (a.nC <= 4) DA_MERGE(DD, DELTA, 4); \
+    else if (four) DA_MERGE(DD, DELTA, 4);   \
     else DA_MERGE(DD, DELTA, 8);             \
   } while (0)
     if (a.d == 128) {

@@ -7,7 +7,7 @@ import pytest
 import torch
 
 import oracle
-from sampling import least_workspace, to_oracle_bits
+from sampling import assert_parity, gather_rows, least_workspace, sample_rows, to_oracle_bits
 
 pytestmark = pytest.mark.gpu
 
@@ -106,3 +106,25 @@ def test_steps_agree_on_the_layout_whatever_smaller_workspace_each_is_given(fuse
     for bits in order:
         run(out, full, bits)
     assert torch.equal(out, whole)
+
+
+@pytest.mark.parametrize("N,Hq,Hkv,d,gamma,chunks", [(14000, 64, 8, 64, 4, 6), (16500, 32, 8, 128, 8, 7)])
+def test_merge_of_many_rows_matches_the_oracle(N, Hq, Hkv, d, gamma, chunks):
+    """Five to eight key chunks and more rows than the merge takes eight at a time:
+    sampled rows, and every anchor row (the merged dense row) against the dense kernel."""
+    b = B()
+    assert b.launch_plan(1, N, Hq, Hkv, d, gamma)["key_chunks"] == chunks
+    assert Hq * (N // gamma) * (d // 4) >= 1 << 21
+    q, k, v, cu = make((N,), Hq, Hkv, d, seed=N)
+    kw = dict(window=300, n_sink=5, gamma=gamma)
+    qd, kd, vd = (x.to(DEV) for x in (q, k, v))
+    out = b.delta_attn_prefill(qd, kd, vd, **kw)
+    dense = b.dense_causal_attn_prefill(qd, kd, vd)
+    a = torch.arange(0, N // gamma * gamma, gamma, device=DEV)
+    # (outputs below 1/8 past the first rows: half a bf16 ulp each, and weights in bf16)
+    diff = (out[a] - dense[a]).float().abs()
+    assert float((diff - 2.0 ** -7 * dense[a].float().abs()).max()) <= 4e-3
+    rows = sample_rows((N,), Hq, 300, 5, gamma, n_random=48, seed=2)
+    ref = oracle.delta_attention_rows(*(to_oracle_bits(x) for x in (q, k, v)), cu.numpy().astype(np.int64),
+                                      rows=rows, **kw)
+    assert_parity(gather_rows(out, [0, N], rows), ref, "delta path")
