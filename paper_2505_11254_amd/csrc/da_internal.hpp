@@ -83,6 +83,7 @@ struct Args {
   // them the head group (s % turn) * turn_step + s / turn
   int n_sub, turn, turn_step;
   FastDiv fd_sub, fd_turn;
+  int ramp;           // row tiles short of a whole key set, which run last (sparse rows)
   int xcd_log;        // log2 of the logical blocks an XCD takes in a row (set by the launcher)
   // Dense-row workgroup order when every sequence has the same length (set by
   // launch_dense_rows; dr_n1 = 0 keeps the plain order).  Row tiles

@@ -261,10 +261,17 @@ __device__ __forceinline__ void attn_body(const Args& a, uint32_t bid, uint32_t 
   // Longest rows first.  In the dense modes blocks dispatched together then have
   // (nearly) the same number of key tiles, start on the same tile and stay in
   // step, so they share each key/value tile in L2.  In the sparse mode the rows
-  // short of a whole window come last and fill the CUs' uneven ends (32K tokens,
-  // window 2048 1176 -> 1156 us the whole call; packed prompts up to 3071 tokens
-  // 223 -> 213 us; 64K tokens over vertical-slash lists 2805 -> 2670 us; 12K
-  // tokens 348 -> 350 us).
+  // short of a whole window come last, the longest of them first, and fill the
+  // CUs' uneven ends (32K tokens, window 2048 1176 -> 1156 us the whole call; packed
+  // prompts up to 3071 tokens 223 -> 213 us); those with a whole window run in
+  // ascending order, as the tiles in them do, so that the keys that neighbouring
+  // slabs share are still in L2.  Against descending order all through: GQA 3,
+  // gamma 48, 20K tokens 408 -> 394 us; sparse rows, 8 heads, three sequences of
+  // 92-182K tokens 4000 -> 3891 us; 32 heads, window 4096, five of 6-18K 4152 ->
+  // 4021 us; 4 heads, 100K tokens 265 -> 255 us; 131K tokens, 32 heads 6192 -> 6181 us,
+  // 32K 1181 -> 1187 us.  Over key-block lists, whose short rows the host does not
+  // know, all rows run in descending order (64K tokens, vertical-slash 2805 -> 2670 us
+  // against ascending; with 2048 keys taken for the ramp 2744 -> 2813 us).
   if (MODE == kDenseRows && a.dr_n1 > 0) {
     // Sequences of one length: every (row tile, chunk) pair that takes a whole
     // key chunk runs before any that takes part of one.  The whole-chunk
@@ -285,7 +292,7 @@ __device__ __forceinline__ void attn_body(const Args& a, uint32_t bid, uint32_t 
       return;  // no key of any chunk is visible to this pair (uniform over the block)
     }
   } else {
-    rt = a.n_rtiles - 1 - rt;
+    rt = MODE == kSparse && rt < a.n_rtiles - a.ramp ? rt + a.ramp : a.n_rtiles - 1 - rt;
   }
 
   const Seq sq = seq_of(a, b);
@@ -1537,6 +1544,8 @@ void prepare_attn(Args& a, int64_t nblocks) {
   }
   a.fd_sub = make_fastdiv((uint32_t)a.n_sub);
   a.fd_turn = make_fastdiv((uint32_t)a.turn);
+  const int64_t rpb = kRowsPerWave * a.ppw, keys = (int64_t)a.window + a.n_sink;
+  a.ramp = a.blk_ptr ? a.n_rtiles : (int)std::min<int64_t>(a.n_rtiles, (keys + rpb - 1) / rpb);
   a.xcd_log = 0;
   const int64_t rounds = a.cu && a.B > 1 ? 64 : 4;
   if (MODE == kSparse && kRowsPerWave * a.ppw * 8 >= kXcdSpread * a.n_hgroups)
