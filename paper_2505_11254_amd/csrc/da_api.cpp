@@ -202,10 +202,9 @@ constexpr int64_t kListKeys = 2048;  // keys of a row under key-block lists, as 
 
 // Wavefronts per attention workgroup: kAttnWaves, or half of them.  `blocks` is
 // the launch in 8-wave workgroups, `work` its tiles in units of the longest of
-// them, `keys` the keys of a sparse row, `even` whether nearly all workgroups
-// are that long.  Outputs
-// are bitwise the same either way: a wavefront runs the same rows over the same
-// tiles.
+// them, `keys` the keys of a sparse row, `shape` how long the workgroups are and how
+// they come.  Outputs are bitwise the same either way: a wavefront runs the same rows
+// over the same tiles.
 //
 // Half-size workgroups fit a CU twice at d = 128 (registers: one wavefront per
 // SIMD each), so that one's first loads and last stores run beside the other's
@@ -236,16 +235,47 @@ constexpr int64_t kListKeys = 2048;  // keys of a row under key-block lists, as 
 //     (0.8), 8 heads, gamma 32, 32768 tokens 208 -> 188 us (1.0); past it even
 //     workgroups, of which half a round may be left: 64 heads, gamma 32, 14848
 //     tokens 314 -> 322 us (1.53), 32 heads, 49945 tokens 1314 -> 1334 us (3.7).
+//   d = 128, flat work below a round of the CUs, whose full-size workgroups all run at
+//     once: a CU that gets two half-size ones takes as long as with a full-size one, so
+//     they pay only while most CUs get one.  Sparse rows: 7791 tokens, 4 heads on 1 (0.41)
+//     54.7 -> 45.4 us, 9729, 4 on 2, window 1600 (0.55) 46.6 -> 46.0 us, 6390, 8 heads
+//     (0.65) 59.8 -> 64.0 us, 12800, 4 on 2, window 4096 (0.65) 104 -> 115 us, 7725, 8 on
+//     4 (0.82) 64.2 -> 68.7 us; but 11382, 6 on 2, window 1600, 270 workgroups of eight
+//     (0.98) 76.4 -> 62.5 us;
+//   d = 128, uneven work of 16 head groups, of which each XCD runs the second after the
+//     first, so that the long half-size workgroups of the one meet those of the other:
+//     from 14 row tiles per head on.  Dense, 16 kv heads: 766 tokens, 64 heads (12) 24.7
+//     -> 22.0 us, 3277, 16 heads (13) 74.9 us both, 3361 (14) 76.2 -> 78.8 us, 4243 (17) 95.9
+//     -> 110 us, 1232, 64 heads (20) 35.8 -> 39.0 us, 2988, 32 heads (24) 0.92 of the time;
+//     with four or more groups in turn neither size is the better one throughout.
+struct Shape {
+  bool even = false;     // nearly all workgroups are as long as the longest
+  bool flat = false;     // most are
+  bool in_turn = false;  // each XCD runs two head groups one after the other
+  bool shared = false;   // another launch's workgroups fill what it leaves, or some of
+                         // those counted are empty (packed sequences)
+};
 int attn_waves(Launch kind, int d, int heads, int64_t blocks, int64_t work, int64_t keys,
-               bool even) {
+               Shape shape) {
   constexpr int kHalf = kAttnWaves / 2;
   if (d == 64) return kHalf;
   if (kind == Launch::kSparseRows && keys <= (heads == 1 ? 1600 : 600)) return kHalf;
-  if (work * 5 < kCUs * 4 || (kind == Launch::kStridedRows && work <= kCUs * 11 / 8)) return kHalf;
+  // flat work of full-size workgroups that all run at once
+  const bool at_once = shape.flat && blocks <= kCUs && !shape.shared;
+  if (!shape.flat && shape.in_turn && blocks * 8 >= kCUs * 7 && work < kCUs) return kAttnWaves;
+  if (work * 5 < kCUs * (at_once ? 3 : 4) || (kind == Launch::kStridedRows && work <= kCUs * 11 / 8)) return kHalf;
+  if (at_once) return kAttnWaves;
   if (work > 4 * kCUs || kind == Launch::kDenseCausal) return kAttnWaves;
-  const int64_t part = (even ? blocks : work) % kCUs * 100 / kCUs;  // of a round, in hundredths
-  const int64_t least = even ? 1 : 28, most = kind == Launch::kStridedRows ? 50 : 72;
+  const int64_t part = (shape.even ? blocks : work) % kCUs * 100 / kCUs;  // of a round, in hundredths
+  const int64_t least = shape.even ? 1 : 28, most = kind == Launch::kStridedRows ? 50 : 72;
   return part >= least && part <= most ? kHalf : kAttnWaves;
+}
+
+Shape shape_of(const Problem& P, int heads, bool even, bool flat, bool shared) {
+  shared |= P.cu && P.B > 1;
+  // (the order of the head groups: see prepare_attn; of eight heads each, whose half-size
+  // workgroups take four, neither size is the better one)
+  return {even, flat, !shared && heads < 8 && P.Hq / heads == 16 && P.Hkv % 16 == 0, shared};
 }
 
 // Tiling of a launch over `rows` rows per (sequence, head) by workgroups of
@@ -265,8 +295,8 @@ int64_t full_blocks(const Problem& P, int hpw) {
 }
 
 // Tiles the sparse launch; in the fused schedule gamma and the list blocks bind
-// the row slab.
-void tile_sparse(Args& a, const Problem& P, bool fused) {
+// the row slab.  shared: it may run together with the strided rows.
+void tile_sparse(Args& a, const Problem& P, bool fused, bool shared) {
   const int G = P.Hq / P.Hkv;
   const int max_rows = P.blk_ptr ? P.block_q : INT32_MAX;
   auto heads = [&](int waves) {
@@ -278,7 +308,8 @@ void tile_sparse(Args& a, const Problem& P, bool fused) {
   const int64_t blocks = full_blocks(P, h8);
   const int64_t ramp = keys < P.N ? keys : P.N;
   const int64_t work = blocks * (2 * (int64_t)P.N - ramp) / (2 * (int64_t)P.N);
-  int waves = attn_waves(Launch::kSparseRows, P.d, h8, blocks, work, keys, P.N >= 4 * keys);
+  const Shape shape = shape_of(P, h8, P.N >= 4 * keys, (int64_t)P.N * 5 >= keys * 14, shared);
+  int waves = attn_waves(Launch::kSparseRows, P.d, h8, blocks, work, keys, shape);
   // Two half-size workgroups share a CU's 160 KB of LDS only if each stages at most
   // 16 KB of dense rows beside its 64 KB ring: 128 / gamma rows of 512 bytes at
   // d = 128, so not at gamma 2 (3 does not divide a slab).  There they pay only while
@@ -301,7 +332,8 @@ void tile_dense(Args& a, const Problem& P) {
   const int G = P.Hq / P.Hkv;
   const int h8 = heads_per_block(G);
   const int64_t work = full_blocks(P, h8) / 2;
-  const int waves = attn_waves(Launch::kDenseCausal, P.d, h8, 2 * work, work, 0, false);
+  const Shape shape = shape_of(P, h8, false, false, false);
+  const int waves = attn_waves(Launch::kDenseCausal, P.d, h8, 2 * work, work, 0, shape);
   set_tiling(a, waves, heads_per_block(G, waves), P.N);
 }
 
@@ -310,7 +342,8 @@ void tile_strided(Args& a, const Problem& P, const Plan& plan) {
   const int G = P.Hq / P.Hkv;
   const int64_t tail = P.cu ? (int64_t)plan.nR_max - plan.nA_max : P.N % P.gamma;
   const int64_t work = strided_tiles(P.B, P.N, P.Hq, G, P.gamma, tail) / (plan.chunk / kKeyTile);
-  const int waves = attn_waves(Launch::kStridedRows, P.d, heads_per_block(G), work, work, 0, true);
+  const Shape shape = shape_of(P, heads_per_block(G), true, true, false);
+  const int waves = attn_waves(Launch::kStridedRows, P.d, heads_per_block(G), work, work, 0, shape);
   set_tiling(a, waves, heads_per_block(G, waves), plan.nR_max);
 }
 
@@ -363,7 +396,7 @@ da_status run_plain(const Problem& P, bool sparse, void* stream) {
   if (st != DA_OK) return st;
   Args a = base_args(P);
   if (sparse)
-    tile_sparse(a, P, false);
+    tile_sparse(a, P, false, false);
   else
     tile_dense(a, P);
   hipError_t e = sparse ? launch_sparse(a, (hipStream_t)stream) : launch_dense(a, (hipStream_t)stream);
@@ -491,14 +524,14 @@ da_status run_delta(const Problem& P, void* workspace, size_t workspace_bytes, v
     }
     if (steps & DA_STEP_SPARSE) {
       Args as = a;
-      tile_sparse(as, P, true);
+      tile_sparse(as, P, true, false);
       e = launch_sparse(as, s);
       if (e != hipSuccess) return fail_hip(e);
     }
     return DA_OK;
   }
   Args as = a, ar = a;
-  tile_sparse(as, P, false);
+  tile_sparse(as, P, false, true);
   tile_strided(ar, P, plan);
   const unsigned both = DA_STEP_SPARSE | DA_STEP_DENSE_ROWS;
   const bool pair = (steps & both) == both && paired(as, ar);
@@ -694,9 +727,9 @@ da_status da_launch_workgroups(int B, int max_seqlen, int packed, int Hq, int Hk
   da::Args as = da::base_args(P), ar, base, dense;
   as.nC = plan.nC;
   ar = base = dense = as;
-  da::tile_sparse(as, P, fused);
+  da::tile_sparse(as, P, fused, !fused);
   da::tile_strided(ar, P, plan);
-  da::tile_sparse(base, P, false);
+  da::tile_sparse(base, P, false, false);
   da::tile_dense(dense, P);
   w->sparse_waves = as.hpw * as.ppw;
   w->sparse_heads = as.hpw;

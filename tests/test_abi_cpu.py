@@ -270,6 +270,21 @@ def test_launch_workgroups_name_the_launches_that_run(lib):
         assert lib.da_launch_workgroups(*args, ctypes.byref(p)) == status, (i, v)
 
 
+@pytest.mark.parametrize("N,Hq,Hkv,window,sparse,dense", [
+    (6390, 8, 8, 2048, 8, 4), (12800, 4, 2, 4096, 8, 4), (7791, 4, 1, 2048, 4, 4),  # rows with whole windows
+    (3236, 16, 2, 2048, 4, 4), (11382, 6, 2, 1600, 4, 4),  # short rows; 270 full-size workgroups
+    (4243, 16, 16, 4096, 8, 8), (3276, 16, 16, 4096, 4, 4), (4243, 16, 8, 4096, 4, 4)])  # two kv heads per XCD
+def test_half_size_workgroups_where_they_pay(lib, N, Hq, Hkv, window, sparse, dense):
+    """Launches below a round of the CUs at d = 128: half-size workgroups where they spread
+    uneven work, full-size ones where two half-size ones would share a CU for as long."""
+    from paper_2505_11254_amd import binding
+    w = binding.launch_workgroups(1, N, Hq, Hkv, 128, 64, window=window, n_sink=16)
+    assert (w["base_waves"], w["dense_waves"]) == (sparse, dense)
+    # (with the strided rows in the same launch those fill the CUs)
+    w = binding.launch_workgroups(1, N, Hq, Hkv, 128, 64, window=window, n_sink=16, mode=3)
+    assert w["sparse_waves"] == 4
+
+
 def test_noalloc_call_validates_and_bounds_its_scratch_before_the_gpu(lib):
     """The allocation-free entry point rejects bad arguments like the others,
     and a problem whose workspace cannot fit its static array (even with one
