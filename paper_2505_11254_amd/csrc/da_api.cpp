@@ -104,6 +104,14 @@ static int64_t strided_tiles(int64_t B, int64_t N, int Hq, int G, int64_t gamma,
 // 30.7 -> 20.4 us; 16 heads d 64 300 tokens 18.0 -> 19.3 us; 32 heads d 128 300
 // tokens 24.5 -> 25.4 us, 520 tokens 30.8 -> 26.7 us.  (At 400 tokens two chunks
 // would take 7-13 % less already: 26.9 -> 24.1 us, 21.4 -> 20.0 us.)
+// Each chunk also costs a partial per row, written and read again.  Where the anchors'
+// are many (gamma 1 to 8: 12.5 MB a chunk at d = 128, twice that at d = 64) and chunks of
+// 2560 keys give the CUs 0.65 rounds of work, that outweighs what finer ones gain:
+// finer -> long, 3 -> 2 chunks, 32 heads, gamma 2, 2814 tokens 125 -> 119 us; 5 -> 3, 9
+// heads, 6008 tokens 112 -> 102 us; 2 -> 1, 40 heads, gamma 1, 2122 tokens 117 -> 95 us;
+// packed, 6 -> 4, 12 heads, gamma 7, 8248 tokens 297 -> 256 us.  Below that: 0.49 rounds,
+// 4 -> 2, 32 heads, gamma 4, 3402 tokens 82.7 -> 85.7 us; 10 MB, 6 -> 4, 8 heads, gamma 4,
+// 8437 tokens 84.5 -> 93.7 us.
 // nC drops only when the partial results would pass kPartialBudget, or, with a nonzero
 // `limit`, until the whole workspace fits `limit` bytes (false when even one
 // chunk does not).  long_chunks: chunks of at least kLongChunk tiles whatever
@@ -120,13 +128,19 @@ bool make_plan(int B, int max_seqlen, int Hq, int Hkv, int d, int gamma, Plan* p
   const int64_t places = B == 1 ? kCUs : kCUs * 3 / 2;
   int64_t min_tiles = (work + places - 1) / places;
   min_tiles = min_tiles < kShortChunk ? kShortChunk : min_tiles > kLongChunk ? kLongChunk : min_tiles;
+  // (every chunk writes a partial per row, and the merge reads it)
+  const int64_t row_bytes = (int64_t)(d + 2) * 4, per_chunk_anchors = (int64_t)B * Hq * nA_max * row_bytes;
+  const int64_t n_long = (max_seqlen + kKeyTile * kLongChunk - 1) / (kKeyTile * kLongChunk);
+  const int64_t long_tiles = ((max_seqlen + n_long - 1) / n_long + kKeyTile - 1) / kKeyTile;
+  if (per_chunk_anchors * d >= (int64_t)12500000 * 128 && work * 100 >= long_tiles * kCUs * 65)
+    min_tiles = kLongChunk;
   constexpr int64_t one = 448;  // keys
   const int64_t min_keys = long_chunks ? kKeyTile * kLongChunk
                            : max_seqlen <= one ? one : kKeyTile * min_tiles;
   int64_t nC = (max_seqlen + min_keys - 1) / min_keys;
   if (nC > 16) nC = 16;
   if (nC < 1) nC = 1;
-  const int64_t per_chunk_bytes = (int64_t)B * Hq * nR_max * (d + 2) * 4;
+  const int64_t per_chunk_bytes = (int64_t)B * Hq * nR_max * row_bytes;
   while (nC > 1 && per_chunk_bytes * nC > kPartialBudget) --nC;
   auto up = [](size_t x) { return (x + 255) / 256 * 256; };
   auto fill = [&](int64_t want) {

@@ -285,6 +285,15 @@ def test_half_size_workgroups_where_they_pay(lib, N, Hq, Hkv, window, sparse, de
     assert w["sparse_waves"] == 4
 
 
+@pytest.mark.parametrize("B,N,Hq,Hkv,d,gamma,chunks", [
+    (1, 7036, 8, 8, 128, 2, 3), (1, 2814, 32, 8, 128, 2, 2), (1, 6008, 9, 3, 128, 2, 3), (4, 1427, 64, 8, 128, 4, 1),
+    # fewer rows, less work, large gamma, half the head size: finer than 2560 keys
+    (1, 2061, 24, 8, 128, 4, 4), (1, 3402, 32, 8, 128, 4, 4), (8, 3071, 32, 8, 128, 64, 3), (1, 3897, 32, 16, 64, 4, 4)])
+def test_many_partials_keep_the_key_chunks_long(lib, B, N, Hq, Hkv, d, gamma, chunks):
+    from paper_2505_11254_amd import binding
+    assert binding.launch_plan(B, N, Hq, Hkv, d, gamma)["key_chunks"] == chunks
+
+
 def test_noalloc_call_validates_and_bounds_its_scratch_before_the_gpu(lib):
     """The allocation-free entry point rejects bad arguments like the others,
     and a problem whose workspace cannot fit its static array (even with one
