@@ -351,13 +351,42 @@ void tile_dense(Args& a, const Problem& P) {
   set_tiling(a, waves, heads_per_block(G, waves), P.N);
 }
 
+// Strided workgroups of `waves` wavefronts that have a key to look at, in one
+// sequence of P.N tokens.
+int64_t strided_with_keys(const Problem& P, const Plan& plan, int64_t tail, int waves) {
+  const int hpw = heads_per_block(P.Hq / P.Hkv, waves);
+  const int64_t rpb = kRowsPerWave * (waves / hpw), rows = plan.nA_max + tail;
+  int64_t n = 0;
+  for (int64_t r0 = 0; r0 < rows; r0 += rpb) {
+    const int64_t last = (r0 + rpb < rows ? r0 + rpb : rows) - 1;
+    n += ((last < plan.nA_max ? last * P.gamma + 1 : P.N) + plan.chunk - 1) / plan.chunk;
+  }
+  return n * (P.Hq / hpw);
+}
+
 // Tiles the strided dense rows: nR_max rows, nC chunks of `chunk` keys.
-void tile_strided(Args& a, const Problem& P, const Plan& plan) {
+// sparse_waves: of the sparse rows' workgroups, 0 where those run by themselves.
+// Up to 1.4 rounds of the CUs, where attn_waves takes half-size workgroups:
+//  - next to sparse rows of full-size workgroups they take full-size ones as well,
+//    which lets one launch run both (moving average, 32 heads, 9000 tokens 253 -> 225
+//    us; gamma 48, 12 heads, 7194 tokens 154 -> 130 us, 8 heads, 35539 429 -> 377 us);
+//  - so they do where the full-size ones run all at once and the half-size ones would
+//    share the CUs, as in attn_waves (2 heads, gamma 64, 175872 tokens 429 -> 378 us; 8
+//    heads, gamma 2, 7036 tokens 134 -> 127 us).
+void tile_strided(Args& a, const Problem& P, const Plan& plan, int sparse_waves) {
   const int G = P.Hq / P.Hkv;
   const int64_t tail = P.cu ? (int64_t)plan.nR_max - plan.nA_max : P.N % P.gamma;
   const int64_t work = strided_tiles(P.B, P.N, P.Hq, G, P.gamma, tail) / (plan.chunk / kKeyTile);
-  const Shape shape = shape_of(P, heads_per_block(G), true, true, false);
-  const int waves = attn_waves(Launch::kStridedRows, P.d, heads_per_block(G), work, work, 0, shape);
+  Shape shape;
+  shape.even = true;
+  int waves = attn_waves(Launch::kStridedRows, P.d, heads_per_block(G), work, work, 0, shape);
+  if (P.d == 128 && work <= kCUs * 11 / 8) {
+    if (sparse_waves)
+      waves = sparse_waves;
+    else if (P.B * strided_with_keys(P, plan, tail, kAttnWaves) <= kCUs &&
+             P.B * strided_with_keys(P, plan, tail, kAttnWaves / 2) * 5 > kCUs * 6)
+      waves = kAttnWaves;
+  }
   set_tiling(a, waves, heads_per_block(G, waves), plan.nR_max);
 }
 
@@ -527,7 +556,7 @@ da_status run_delta(const Problem& P, void* workspace, size_t workspace_bytes, v
     const bool direct = plan.nC == 1 && (steps & both) == both;
     if (steps & DA_STEP_DENSE_ROWS) {
       Args ar = a;
-      tile_strided(ar, P, plan);
+      tile_strided(ar, P, plan, 0);
       ar.merged = direct;
       e = launch_dense_rows(ar, s);
       if (e != hipSuccess) return fail_hip(e);
@@ -546,7 +575,7 @@ da_status run_delta(const Problem& P, void* workspace, size_t workspace_bytes, v
   }
   Args as = a, ar = a;
   tile_sparse(as, P, false, true);
-  tile_strided(ar, P, plan);
+  tile_strided(ar, P, plan, as.hpw * as.ppw);
   const unsigned both = DA_STEP_SPARSE | DA_STEP_DENSE_ROWS;
   const bool pair = (steps & both) == both && paired(as, ar);
   if (pair) as.rows = &ar;
@@ -742,7 +771,7 @@ da_status da_launch_workgroups(int B, int max_seqlen, int packed, int Hq, int Hk
   as.nC = plan.nC;
   ar = base = dense = as;
   da::tile_sparse(as, P, fused, !fused);
-  da::tile_strided(ar, P, plan);
+  da::tile_strided(ar, P, plan, fused ? 0 : as.hpw * as.ppw);
   da::tile_sparse(base, P, false, false);
   da::tile_dense(dense, P);
   w->sparse_waves = as.hpw * as.ppw;

@@ -294,6 +294,16 @@ def test_many_partials_keep_the_key_chunks_long(lib, B, N, Hq, Hkv, d, gamma, ch
     assert binding.launch_plan(B, N, Hq, Hkv, d, gamma)["key_chunks"] == chunks
 
 
+@pytest.mark.parametrize("N,Hq,Hkv,window,gamma,mode,rows,together", [
+    (175872, 2, 2, 256, 64, 0, 8, 0), (7036, 8, 8, 1600, 2, 0, 8, 0),  # all at once
+    (5406, 24, 8, 256, 64, 0, 4, 0), (48091, 8, 4, 256, 64, 0, 4, 0),  # half empty; more than one round
+    (9000, 32, 8, 1024, 64, 3, 8, 1), (3000, 32, 8, 256, 64, 3, 4, 1)])  # next to the sparse rows
+def test_strided_workgroups_where_full_size_ones_pay(lib, N, Hq, Hkv, window, gamma, mode, rows, together):
+    from paper_2505_11254_amd import binding
+    w = binding.launch_workgroups(1, N, Hq, Hkv, 128, gamma, window=window, n_sink=16, mode=mode)
+    assert (w["rows_waves"], w["together"]) == (rows, together)
+
+
 def test_noalloc_call_validates_and_bounds_its_scratch_before_the_gpu(lib):
     """The allocation-free entry point rejects bad arguments like the others,
     and a problem whose workspace cannot fit its static array (even with one
