@@ -212,7 +212,8 @@ da_status validate(const Problem& P, bool need_window, bool need_gamma) {
 }
 
 enum class Launch { kSparseRows, kDenseCausal, kStridedRows };
-constexpr int64_t kListKeys = 2048;  // keys of a row under key-block lists, as a typical guess
+// Keys of a row under key-block lists, as a typical guess: the lists are on the device.
+constexpr int64_t kListKeys = 2048;
 
 // Wavefronts per attention workgroup: kAttnWaves, or half of them.  `blocks` is
 // the launch in 8-wave workgroups, `work` its tiles in units of the longest of

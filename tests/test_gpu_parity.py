@@ -291,10 +291,10 @@ def test_workload_llama8b_1m_stratified():
 
 @pytest.mark.timeout(600)
 def test_interleaved_xcd_map_at_scale():
-    """Head groups that do not split evenly over the 8 XCDs (here 4 groups of one
-    head) take the interleaved-chunk block map, which only engages on grids of
-    at least 512 blocks: 64K tokens give 1024 sparse blocks and a strided grid
-    of the same order; checked on sampled rows, sparse and Delta outputs."""
+    """So few head groups that neighbouring slabs of an XCD would lie far apart (here 4
+    groups of one head) give the sparse rows the interleaved-chunk block map, in full
+    at 64K tokens (2048 sparse blocks); the strided rows take the heads in turn.  Checked
+    on sampled rows, sparse and Delta outputs."""
     from paper_2505_11254_amd.inputs import random_qkv
     L, Hq, Hkv, d, w, s, gamma = 65536, 4, 4, 64, 512, 16, 32
     q, k, v, cu = random_qkv((L,), Hq, Hkv, d, seed=41, device=DEV)

@@ -63,8 +63,8 @@ def rounding_slack(ref, ref_sp, unfused):
 
 
 def draw_long(seed):
-    """A configuration long enough for several key chunks per dense row (a chunk
-    holds at least 2560 keys): 2.5K-24K tokens, GQA 1-4, gamma 8-129."""
+    """A configuration long enough for several key chunks per dense row, of 2560 keys
+    too: 2.5K-24K tokens, GQA 1-4, gamma 8-129."""
     rng = np.random.default_rng(seed)
     B = int(rng.integers(1, 4))
     if rng.random() < 0.4:
