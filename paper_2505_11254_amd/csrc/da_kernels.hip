@@ -291,12 +291,20 @@ __device__ __forceinline__ void attn_body(const Args& a, uint32_t bid, uint32_t 
     } else {
       return;  // no key of any chunk is visible to this pair (uniform over the block)
     }
-  } else {
-    rt = MODE == kSparse && rt < a.n_rtiles - a.ramp ? rt + a.ramp : a.n_rtiles - 1 - rt;
+  } else if (MODE != kSparse) {
+    rt = a.n_rtiles - 1 - rt;
   }
 
   const Seq sq = seq_of(a, b);
   const int L = sq.L;
+  const int rows_per_block = kRowsPerWave * a.ppw;
+  if (MODE == kSparse) {
+    // (the places that a shorter sequence of a packed batch leaves empty come first)
+    const int nt = min(a.n_rtiles, (L + rows_per_block - 1) >> __builtin_ctz(rows_per_block));
+    rt -= a.n_rtiles - nt;
+    if (rt < 0) return;  // uniform over the block
+    rt = rt < nt - a.ramp ? rt + a.ramp : nt - 1 - rt;
+  }
   // hpw is a power of two: head in block = wave % hpw, sub-tile = wave / hpw
   const int hpw_log = __builtin_ctz(a.hpw);
   const int h = hg * a.hpw + (wave & (a.hpw - 1));
@@ -306,7 +314,6 @@ __device__ __forceinline__ void attn_body(const Args& a, uint32_t bid, uint32_t 
   const int Lc = nA * a.gamma;
   const int n_rows = (MODE == kDenseRows) ? nA + (L - Lc) : L;
 
-  const int rows_per_block = kRowsPerWave * a.ppw;
   const int R0 = rt * rows_per_block;
   if (R0 >= n_rows) return;  // uniform over the block
   const int R1 = min(R0 + rows_per_block, n_rows);
