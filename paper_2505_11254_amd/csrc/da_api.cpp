@@ -112,6 +112,11 @@ static int64_t strided_tiles(int64_t B, int64_t N, int Hq, int G, int64_t gamma,
 // packed, 6 -> 4, 12 heads, gamma 7, 8248 tokens 297 -> 256 us.  Below that: 0.49 rounds,
 // 4 -> 2, 32 heads, gamma 4, 3402 tokens 82.7 -> 85.7 us; 10 MB, 6 -> 4, 8 heads, gamma 4,
 // 8437 tokens 84.5 -> 93.7 us.
+// Nor do chunks of fewer than 8 tiles pay where they make more workgroups than there are
+// CUs, whose fixed cost is several tiles: at d = 128 there are no more chunks then than a
+// round of full-size workgroups holds.  Packed, 40 heads, gamma 2, 537 + 515 tokens 51.8
+// -> 41.5 us (3 chunks -> 1), ten up to 493 tokens, 16 heads 50.5 -> 41.6 us (2 -> 1); 8
+// heads, gamma 7, 4776 tokens 81.8 -> 65.1 us; with d = 64 included 0.91-1.06 there.
 // nC drops only when the partial results would pass kPartialBudget, or, with a nonzero
 // `limit`, until the whole workspace fits `limit` bytes (false when even one
 // chunk does not).  long_chunks: chunks of at least kLongChunk tiles whatever
@@ -123,7 +128,7 @@ bool make_plan(int B, int max_seqlen, int Hq, int Hkv, int d, int gamma, Plan* p
   if (Hq % Hkv != 0) return false;
   const int64_t nA_max = max_seqlen / gamma;
   const int64_t nR_max = nA_max + (int64_t)((gamma - 1 < max_seqlen) ? gamma - 1 : max_seqlen);
-  constexpr int64_t kLongChunk = 40, kShortChunk = 2;  // tiles
+  constexpr int64_t kLongChunk = 40, kShortChunk = 2, kFewTiles = 8;  // tiles
   const int64_t work = strided_tiles(B, max_seqlen, Hq, Hq / Hkv, gamma, nR_max - nA_max);
   const int64_t places = B == 1 ? kCUs : kCUs * 3 / 2;
   int64_t min_tiles = (work + places - 1) / places;
@@ -140,6 +145,14 @@ bool make_plan(int B, int max_seqlen, int Hq, int Hkv, int d, int gamma, Plan* p
   int64_t nC = (max_seqlen + min_keys - 1) / min_keys;
   if (nC > 16) nC = 16;
   if (nC < 1) nC = 1;
+  if (d == 128 && !long_chunks) {
+    // (full-size workgroups of one chunk; sequences of a batch have half the tail)
+    const int hpw = heads_per_block(Hq / Hkv);
+    const int64_t rpb = kRowsPerWave * (kAttnWaves / hpw);
+    const int64_t rows = B == 1 ? nR_max : (nA_max + nR_max + 1) / 2;
+    const int64_t blocks = (int64_t)B * (Hq / hpw) * ((rows + rpb - 1) / rpb);
+    while (nC > n_long && nC * blocks > kCUs && max_seqlen < nC * kKeyTile * kFewTiles) --nC;
+  }
   const int64_t per_chunk_bytes = (int64_t)B * Hq * nR_max * row_bytes;
   while (nC > 1 && per_chunk_bytes * nC > kPartialBudget) --nC;
   auto up = [](size_t x) { return (x + 255) / 256 * 256; };

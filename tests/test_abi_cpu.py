@@ -287,6 +287,8 @@ def test_half_size_workgroups_where_they_pay(lib, N, Hq, Hkv, window, sparse, de
 
 @pytest.mark.parametrize("B,N,Hq,Hkv,d,gamma,chunks", [
     (1, 7036, 8, 8, 128, 2, 3), (1, 2814, 32, 8, 128, 2, 2), (1, 6008, 9, 3, 128, 2, 3), (4, 1427, 64, 8, 128, 4, 1),
+    # short chunks that would make more workgroups than there are CUs
+    (2, 537, 40, 8, 128, 2, 1), (10, 493, 16, 16, 128, 128, 1), (1, 4776, 8, 8, 128, 7, 10), (1, 1024, 32, 8, 128, 64, 8),
     # fewer rows, less work, large gamma, half the head size: finer than 2560 keys
     (1, 2061, 24, 8, 128, 4, 4), (1, 3402, 32, 8, 128, 4, 4), (8, 3071, 32, 8, 128, 64, 3), (1, 3897, 32, 16, 64, 4, 4)])
 def test_many_partials_keep_the_key_chunks_long(lib, B, N, Hq, Hkv, d, gamma, chunks):
