@@ -137,7 +137,7 @@ bool make_plan(int B, int max_seqlen, int Hq, int Hkv, int d, int gamma, Plan* p
   const int64_t row_bytes = (int64_t)(d + 2) * 4, per_chunk_anchors = (int64_t)B * Hq * nA_max * row_bytes;
   const int64_t n_long = (max_seqlen + kKeyTile * kLongChunk - 1) / (kKeyTile * kLongChunk);
   const int64_t long_tiles = ((max_seqlen + n_long - 1) / n_long + kKeyTile - 1) / kKeyTile;
-  if (per_chunk_anchors * d >= (int64_t)12500000 * 128 && work * 100 >= long_tiles * kCUs * 65)
+  if (per_chunk_anchors >= (int64_t)12500000 * 128 / d && work * 100 >= long_tiles * kCUs * 65)
     min_tiles = kLongChunk;
   constexpr int64_t one = 448;  // keys
   const int64_t min_keys = long_chunks ? kKeyTile * kLongChunk
